@@ -24,6 +24,9 @@ FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-mcode-object-version=5",
     # no packed fp32 VALU instructions: scalar/float2 code is compiled to unpacked ops
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # MFMA sums in ordinary registers: the attention loop rescales them between MFMAs, and with
+    # accumulation registers every tile copied all of them there and back
+    "-mllvm", "-amdgpu-mfma-vgpr-form",
     "-I", os.path.join(ROOT, "include"),
     "-fvisibility=hidden", "-Wall", "-Wno-unused-function",
 ]

@@ -14,17 +14,13 @@
 // (full / Delta layers) over a ragged batch of 2-64 sequences instead cuts the batch's actual
 // groups, in (b, g, page) order, into equal runs, one per workgroup, each run possibly
 // spanning pairs, so that every CU gets the same work whatever the spread of sequence
-// lengths; with equal or nearly equal lengths the static cut is kept.  Waves take a piece's groups in interleaved blocks of four and keep their
-// own online-softmax state; all G query heads of the KV group share every K/V byte read.
+// lengths; with equal or nearly equal lengths the static cut is kept.  Waves take a piece's
+// groups in interleaved blocks of four and keep their own online-softmax state; all G query
+// heads of the KV group share every K/V byte read.
 //
 // Per group and wave:
-//   * QK^T on the matrix cores: v_mfma_f32_16x16x32_bf16 with A = the 16 K rows (M = rows,
-//     K = head dim) and B = the G query vectors padded to 16 columns; D/32 MFMAs give the
-//     16 x 16 score tile, lane l holding rows 4*(l/16)..+3 of head column l%16.
-//   * online softmax in the log2 domain (exp2, scale folded with log2 e); the group's
-//     probabilities and the per-head rescale factor go through a wave-private LDS slice;
-//   * P.V on the vector ALUs: each lane owns 8 consecutive head-dim columns of 16/RPI rows
-//     (128-bit loads, one V row per LPR consecutive lanes, fully coalesced).
+//   * both contractions on the matrix cores, with an online softmax in the log2 domain between
+//     them that keeps the probabilities in their lane (attn_tile.h);
 //   Each wave keeps a ring of R register tiles: while one group is consumed, the K/V loads of
 //   the next R - 1 groups are in flight.  With logits on, the logits of a chunk of groups are
 //   staged in LDS and written by the whole workgroup between chunks.
@@ -53,7 +49,14 @@ constexpr int kCoherent = 16;
 // MI355X, fewer and larger chunk flushes beat two resident workgroups with half the staging).
 constexpr int kStageFloats = 32768;
 
+// Page list entries of the selected-page mode: the page, and whether only the sequence's tail
+// rows (kPartialPage) or none of its rows (kEmptyPage, the sign bit) exist.
+constexpr int kPageMask = 0x3fffffff;
+constexpr int kPartialPage = 0x40000000;
+constexpr int kEmptyPage = (int)0x80000000;
+
 template <int D, int G, int MODE, bool LOGITS, bool BAL>
+
 __global__ __launch_bounds__(kAttnThreads) void attn_kernel(const AttnArgs a) {
   using Gm = Geo<D>;
   constexpr int R = Gm::R;
@@ -69,14 +72,14 @@ __global__ __launch_bounds__(kAttnThreads) void attn_kernel(const AttnArgs a) {
   // [g0, g0 + cand) of (sequence b, KV head g), requested at once; the list goes to LDS.
   bf16x8 qb[Gm::NK];
   __shared__ int s_rows[kMaxRowSlots];
-  __shared__ int s_aux[MODE == ROWS_SEL_PAGE ? kMaxRowSlots : 1];
   // (Debug builds check every physical page and selected unit here and flag bad ones; see
   // checked_page.)
   auto stage = [&](int b, int g, int g0, int cand) {
     load_query<D, G>(qb, a.q, (size_t)b * Hq + g * G, lane);
     const int32_t* pt = a.page_table + (size_t)b * a.max_pages;
-    // debug builds: the sequence's length bounds its selected units (release: unused)
-    const int s_dbg = DELTA_DEBUG && MODE != ROWS_DENSE ? a.seq_lens[b] : 0;
+    // selected pages: the length says which of them is the partial last one; debug builds also
+    // check the selected units against it
+    const int s_len = MODE == ROWS_SEL_PAGE || (DELTA_DEBUG && MODE != ROWS_DENSE) ? a.seq_lens[b] : 0;
     if (MODE == ROWS_DENSE) {
       for (int i = tid; i < cand; i += kAttnThreads)
         s_rows[i] = checked_page(pt[g0 + i], a.n_pages, a.status);
@@ -88,9 +91,11 @@ __global__ __launch_bounds__(kAttnThreads) void attn_kernel(const AttnArgs a) {
         const int u = sel[g0 + i];
         const int ph = phys ? phys[g0 + i] : 0;
         const bool ok = u >= 0 && u < a.max_pages;
-        if (DELTA_DEBUG && u >= 0 && 16 * u >= s_dbg) debug_flag(a.status, DELTA_DEBUG_SELECTION);
-        s_rows[i] = ok ? checked_page(phys ? ph : pt[u], a.n_pages, a.status) : 0;
-        s_aux[i] = ok ? u : 0;
+        if (DELTA_DEBUG && u >= 0 && 16 * u >= s_len) debug_flag(a.status, DELTA_DEBUG_SELECTION);
+        const int page = ok ? checked_page(phys ? ph : pt[u], a.n_pages, a.status) : 0;
+        // (a page index needs 30 bits at most: a page is at least 2 KB)
+        const int rows = s_len - 16 * (ok ? u : 0);
+        s_rows[i] = page | (rows >= 16 ? 0 : rows > 0 ? kPartialPage : kEmptyPage);
       }
     } else {
       const int32_t* sel = a.sel_idx + (size_t)b * a.sel_stride;
@@ -101,7 +106,7 @@ __global__ __launch_bounds__(kAttnThreads) void attn_kernel(const AttnArgs a) {
         if (i < n_rows) {
           const int t = sel[16 * g0 + i];
           const int ph = phys ? phys[16 * g0 + i] : 0;
-          if (DELTA_DEBUG && t >= s_dbg) debug_flag(a.status, DELTA_DEBUG_SELECTION);
+          if (DELTA_DEBUG && t >= s_len) debug_flag(a.status, DELTA_DEBUG_SELECTION);
           if (t >= 0 && t < 16 * a.max_pages) {
             const int page = checked_page(phys ? ph >> 4 : pt[t >> 4], a.n_pages, a.status);
             packed = page * 16 + (phys ? ph & 15 : t & 15);
@@ -119,14 +124,19 @@ __global__ __launch_bounds__(kAttnThreads) void attn_kernel(const AttnArgs a) {
   };
 
   // shared state of the attention of one piece
-  __shared__ float s_p[kWaves][16 * 8 + 8];   // wave-private: P[16 rows][8 heads], rescale
   constexpr int kChunk = (kStageFloats / (G * 16)) / 16 * 16;
   __shared__ __attribute__((aligned(16))) float s_stage[LOGITS ? kChunk * G * 16 : 1];
   __shared__ float s_m[kWaves][kMaxGroup], s_l[kWaves][kMaxGroup];
-  __shared__ __attribute__((aligned(16))) float s_o[kWaves][G][D];
+  // each wave's K tile on its way to the matrix cores, later its outputs
+  union WaveSpace {
+    uint16_t k[16 * D];
+    float o[G][D];
+  };
+  __shared__ __attribute__((aligned(16))) WaveSpace s_w[kWaves];
   __shared__ int s_last;
 #if DELTA_QK_VALU
   __shared__ __attribute__((aligned(16))) uint16_t s_qv[kWaves][G * D];
+  __shared__ float s_p[kWaves][16 * 8];   // wave-private: the score tile
 #endif
   static_assert(G * D <= 4 * kAttnThreads && D % 4 == 0, "four outputs per thread cover a group");
 
@@ -140,38 +150,39 @@ __global__ __launch_bounds__(kAttnThreads) void attn_kernel(const AttnArgs a) {
     // Loads tile `li` of the piece.  A prefetch past the wave's last group (real == false) is
     // still issued, so that the loop's memory waits stay uniform, but with every lane at the
     // tile's first 16 bytes: one cache line per load instruction instead of a whole tile.
-    auto load_tile = [&](Tile<D>& t, int li, bool real) {
+    // `row` is the tile's page list entry (page modes), read from LDS one tile ahead.
+    const int s_last_page = (s_b - 1) >> 4;
+    const uint32_t tail_mask = 0xffffu >> (15 - ((s_b - 1) & 15));   // rows of the last page
+    auto load_tile = [&](Tile<D>& t, int row, int li, bool real) {
       if (MODE == ROWS_SEL_TOKEN) {
         // every row is its own (page, row); rows past the selection re-read the group's first
         const int* rows = s_rows + 16 * li;
-        const int base = 16 * (g0 + li);
         const int first = rows[0];
-        t.kmask = 0;
+        t.kmask = (uint32_t)__ballot(rows[hcol] >= 0 && 16 * (g0 + li) + hcol < sel_n) & 0xffffu;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) t.kmask |= ((rows[r] >= 0 && base + r < sel_n) ? 1u : 0u) << r;
-        const int kr = ((t.kmask >> hcol) & 1u) && real ? rows[hcol] : first;
-        const uint16_t* kp = a.k_cache + (size_t)(kr >> 4) * a.page_stride + head_off +
-                             (size_t)(kr & 15) * D + (real ? 8 * quad : 0);
+        for (int i = 0; i < Gm::NK; ++i) {
+          const int r = k_row<D>(i, lane);
+          const int kr = ((t.kmask >> r) & 1u) && real ? rows[r] : first;
+          t.k[i] = load16_stream(a.k_cache + (size_t)(kr >> 4) * a.page_stride + head_off +
+                                 (size_t)(kr & 15) * D + (real ? 8 * (lane % Gm::CPR) : 0));
+        }
 #pragma unroll
-        for (int ks = 0; ks < Gm::NK; ++ks) t.k[ks] = load16_stream(kp + (real ? 32 * ks : 0));
-#pragma unroll
-        for (int i = 0; i < Gm::NI; ++i) {
-          const int r = Gm::RPI * i + lane / Gm::LPR;
+        for (int i = 0; i < 4; ++i) {
+          const int r = 4 * quad + i;
           const int vr = ((t.kmask >> r) & 1u) && real ? rows[r] : first;
-          t.v[i] = load16_stream(a.v_cache + (size_t)(vr >> 4) * a.page_stride + head_off +
-                                 (size_t)(vr & 15) * D + (real ? 8 * (lane % Gm::LPR) : 0));
+          t.v[i] = load_v_stream<D>(a.v_cache + (size_t)(vr >> 4) * a.page_stride + head_off +
+                                    (size_t)(vr & 15) * D + (real ? Gm::NC * hcol : 0));
         }
       } else {
-        const size_t page = (size_t)s_rows[li] * a.page_stride + head_off;
-        const int unit = (MODE == ROWS_DENSE) ? g0 + li : s_aux[li];
-        const int nrows = min(16, s_b - 16 * unit);
-        t.kmask = (nrows >= 16) ? 0xffffu : ((1u << max(nrows, 0)) - 1u);
+        row = __builtin_amdgcn_readfirstlane(row);
+        const size_t page = (size_t)(row & kPageMask) * a.page_stride + head_off;
+        if (MODE == ROWS_DENSE) t.kmask = g0 + li == s_last_page ? tail_mask : 0xffffu;
+        else t.kmask = row < 0 ? 0u : (row & kPartialPage) ? tail_mask : 0xffffu;
         load_page_tile<D>(t, a.k_cache + page, a.v_cache + page, real, lane);
       }
     };
 
-    float* lp = s_p[wave];
-    WaveSoftmax<G> st;
+    WaveSoftmax<D, G> st;
     st.init();
     const int Hq_row = b * Hq + g * G;
     // Logits on: the workgroup keeps the logits of a chunk of kChunk groups in LDS ([group]
@@ -184,13 +195,14 @@ __global__ __launch_bounds__(kAttnThreads) void attn_kernel(const AttnArgs a) {
     // build option: QK^T on the vector ALUs, the query vectors read from the wave's LDS copy
     stage_query_lds<D, G>(qb, s_qv[wave], lane);
     wave_lds_sync();
-    auto process = [&](const Tile<D>& t, int slot_in_chunk) {
-      process_tile_valu<D, G, LOGITS>(t, s_qv[wave], a.scale_log2, st, lp,
+    auto process = [&](Tile<D>& t, int slot_in_chunk) {
+      process_tile_valu<D, G, LOGITS>(t, s_qv[wave], a.scale_log2, st, s_p[wave], s_w[wave].k,
                                       s_stage + slot_in_chunk * G * 16, lane);
     };
 #else
-    auto process = [&](const Tile<D>& t, int slot_in_chunk) {
-      process_tile<D, G, LOGITS>(t, qb, a.scale_log2, st, lp, s_stage + slot_in_chunk * G * 16, lane);
+    auto process = [&](Tile<D>& t, int slot_in_chunk) {
+      process_tile<D, G, LOGITS>(t, qb, a.scale_log2, st, s_w[wave].k,
+                                 s_stage + slot_in_chunk * G * 16, lane);
     };
 #endif
 
@@ -209,7 +221,15 @@ __global__ __launch_bounds__(kAttnThreads) void attn_kernel(const AttnArgs a) {
       const int n_mine = 4 * full_blocks + min(4, max(0, rem - 4 * wave));
       auto walk = [&](int kb, int ke, int c0) {
         if (kb >= ke) return;
-        auto fetch = [&](Tile<D>& t, int k) { load_tile(t, group_of(min(k, ke - 1)), k < ke); };
+        // (the scheduler must not reorder the loads of different tiles: the compiler's wait for
+        // the oldest tile would then drain the younger ones)
+        int row = s_rows[group_of(kb)];
+        auto fetch = [&](Tile<D>& t, int k) {
+          __builtin_amdgcn_sched_barrier(0);
+          load_tile(t, row, group_of(min(k, ke - 1)), k < ke);
+          row = s_rows[group_of(min(k + 1, ke - 1))];
+          __builtin_amdgcn_sched_barrier(0);
+        };
         Tile<D> t[R];
 #pragma unroll
         for (int i = 0; i < R - 1; ++i) fetch(t[i], kb + i);
@@ -242,19 +262,23 @@ __global__ __launch_bounds__(kAttnThreads) void attn_kernel(const AttnArgs a) {
       }
     }
 
-    // ---- reduce o over the lanes that share a head-dim chunk -----------------------------
-    reduce_outputs<D, G>(st);
+    // ---- add the terms of o and the lanes' sums --------------------------------------------
+    reduce_outputs<D, G>(st, lane);
 
     // ---- merge the 4 waves into one partial of the piece ---------------------------------
     if (quad == 0 && hcol < G) {
       s_m[wave][hcol] = st.m_run;
       s_l[wave][hcol] = st.l_run;
     }
-    if (lane < Gm::LPR) {
+    if (quad < kCopy<G> / 4) {
 #pragma unroll
-      for (int h = 0; h < G; ++h)
+      for (int r = 0; r < 4; ++r) {
+        if (4 * quad + r >= G) break;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) s_o[wave][h][8 * lane + e] = st.o[h][e];
+        for (int c = 0; c < Gm::NC; c += 4)
+          *reinterpret_cast<f32x4*>(&s_w[wave].o[4 * quad + r][Gm::NC * hcol + c]) =
+              f32x4{st.o[c][r], st.o[c + 1][r], st.o[c + 2][r], st.o[c + 3][r]};
+      }
     }
     lds_barrier();
 
@@ -274,7 +298,7 @@ __global__ __launch_bounds__(kAttnThreads) void attn_kernel(const AttnArgs a) {
 #pragma unroll
       for (int w = 0; w < kWaves; ++w) {
         const float f = (s_m[w][h] == kNegInf) ? 0.f : exp2f(s_m[w][h] - M);
-        const f32x4 ow = *reinterpret_cast<const f32x4*>(&s_o[w][h][dc]);
+        const f32x4 ow = *reinterpret_cast<const f32x4*>(&s_w[w].o[h][dc]);
         O += f * ow;
         L += f * s_l[w][h];
       }

@@ -1,14 +1,39 @@
 // Per-tile pieces of the gfx950 decode-attention kernels (Sec. 2, Eq. gqa_attention): loading a
 // 16-row K/V tile of one KV head, and folding it into one wave's online softmax for the G query
-// heads of that KV head.
+// heads of that KV head.  Both contractions run on the matrix cores, and the probabilities go
+// from one to the other without leaving their lane:
 //
-//   * QK^T on the matrix cores: v_mfma_f32_16x16x32_bf16 with A = the 16 K rows (M = rows,
-//     K = head dim) and B = the G query vectors padded to 16 columns; D/32 MFMAs give the
-//     16 x 16 score tile, lane l holding rows 4*(l/16)..+3 of head column l%16.
-//   * online softmax in the log2 domain (exp2, scale folded with log2 e); the tile's
-//     probabilities and the per-head rescale factor go through a wave-private LDS slice;
-//   * P.V on the vector ALUs: each lane owns 8 consecutive head-dim columns of 16/RPI rows
-//     (128-bit loads, one V row per LPR consecutive lanes, fully coalesced).
+//   * K rows come in whole (1 KB of consecutive rows per wave-wide load) and pass through a
+//     wave-private LDS slice into the matrix-core layout, 16 bytes of another row per lane.
+//     Loading that layout straight from memory touches 64 cache lines per load where 8 would do,
+//     which held a CU at 35 GB/s (one 32K sequence, G = 7, 64 workgroups: 36 us against 27 us).
+//   * QK^T: v_mfma_f32_16x16x32_bf16 with A = the 16 K rows (M = rows, K = head dim) and B = the
+//     query vectors (N = 16 columns).  Lane (quad, n) of the score tile holds rows 4*quad ..
+//     4*quad+3 of column n.  Column n carries query head n % S, S = 4 (G <= 4) or 8: every head
+//     stands in 16 / S columns, so 16 / S lanes hold the same scores.
+//   * online softmax in the log2 domain (exp2, scale folded with log2 e).  The running maximum is
+//     raised, and the outputs rescaled, only when a score exceeds it by more than kRaise (a
+//     wave-uniform branch, taken a few times per walk); until then the probabilities are
+//     relative to a maximum that is too low by at most 2^kRaise, which fp32 holds with the same
+//     relative precision.  Each lane sums the probabilities of its own rows.
+//   * P.V: v_mfma_f32_16x16x16_bf16 with A = P (M = columns n of the score tile, K = the 16 rows)
+//     and B = V (N = 16 head-dim columns).  The A operand's lane (quad, m) holds rows 4*quad ..
+//     4*quad+3 of m, which is the score tile's own layout.  An fp32 probability is the exact sum
+//     of three bf16 terms (its upper 8 significant bits, the next 8, the last 8), and the copies
+//     of a head's column carry one term each: with S = 4 three of the four copies make one MFMA,
+//     with S = 8 two terms make one and the third a second one.  V is bf16 as it is, the products
+//     are exact and the sums fp32, so no probability is rounded.  Lane (quad, n) loads 8 (d = 128)
+//     or 4 (d = 64) consecutive columns of rows 4*quad .. 4*quad+3, and MFMA c takes column
+//     (D/16)*n + c from lane n: the operand is two byte permutes of the lane's own registers.
+//
+// Bound: HBM, as soon as the per-tile chain of a wave is shorter than its share of the memory
+// rate.  With P.V on the vector ALUs (32*G fma per tile, P through LDS, a cross-lane maximum and
+// sum per tile) and uncoalesced K loads the chain took 1.1 us per 8 KB tile, i.e. 29 GB/s per CU
+// with one wave per SIMD however many loads were in flight, while a CU alone reads 57 GB/s: grids
+// below 256 workgroups and the few tiles per wave of small launches were bound by it.  Measured
+// on MI355X, before and after (us per layer): one 32K sequence, 28/4 heads, 64 workgroups 43.5 and
+// 26.6; 64 sequences of 600-1500 tokens, 12/2 heads 26.5 and 20.0; 20 sequences of 12289 tokens,
+// 40/8 heads 219 and 183; 32 ragged sequences of 16K-32K, 32/8 heads (3.2 GB) 501 and 485.
 #pragma once
 
 #include "internal.h"
@@ -20,40 +45,52 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef short i16x4 __attribute__((ext_vector_type(4)));
 
 constexpr float kNegInfF = -__builtin_huge_valf();
 
 template <int D>
 struct Geo {
   static constexpr int NK = D / 32;     // MFMA k-steps = 16-byte K loads per lane per tile
-  static constexpr int LPR = D / 8;     // lanes per V row
-  static constexpr int RPI = 64 / LPR;  // V rows per wave-wide load
-  static constexpr int NI = 16 / RPI;   // V loads per lane per tile
+  static constexpr int CPR = D / 8;     // 16-byte pieces of a K row
+  static constexpr int RPL = 64 / CPR;  // K rows per wave-wide load
+  static constexpr int NC = D / 16;     // V columns per lane = P.V MFMAs per tile and term group
+  static constexpr int NW = D / 32;     // 32-bit words of a lane's V columns of one row
   // register tiles per wave: loads of R - 1 tiles stay in flight while one is consumed
   static constexpr int R = D == 128 ? 3 : 4;
 };
 
+template <int W>
+struct VWords;
+template <>
+struct VWords<4> { typedef u32x4 type; };
+template <>
+struct VWords<2> { typedef u32x2 type; };
+
 template <int D>
 struct Tile {
-  u32x4 k[Geo<D>::NK];
-  u32x4 v[Geo<D>::NI];
-  uint32_t kmask;   // bit r: row r valid (rows of the MFMA A operand and of the score tile)
+  u32x4 k[Geo<D>::NK];   // load i: row k_row<D>(i, lane), piece lane % CPR
+  typename VWords<Geo<D>::NW>::type v[4];   // rows 4*quad .. 4*quad+3
+  uint32_t kmask;   // bit r: row r valid (wave-uniform)
 };
 
-// One wave's running softmax state for the G query heads of one KV head: running max and sum
-// of head (lane & 15) (valid for lanes with lane & 15 < G), and the lane's share of the
-// unnormalised outputs (8 head-dim columns of its V rows, for every head).
+// Columns of the score tile per copy of the query heads (column n carries head n % kCopy<G>).
 template <int G>
+constexpr int kCopy = G <= 4 ? 4 : 8;
+
+// One wave's running softmax state for the G query heads of one KV head: the maximum of head
+// n % S in use (the same in every lane of that head), the sum over the lane's own rows, and the
+// unnormalised outputs as P.V leaves them: o[c][r] = row 4*quad + r (a term of head
+// (4*quad + r) % S) of head-dim column NC*n + c.
+template <int D, int G>
 struct WaveSoftmax {
   float m_run, l_run;
-  float o[G][8];
+  f32x4 o[Geo<D>::NC];
   __device__ __forceinline__ void init() {
     m_run = kNegInfF;
     l_run = 0.f;
 #pragma unroll
-    for (int h = 0; h < G; ++h)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) o[h][e] = 0.f;
+    for (int c = 0; c < Geo<D>::NC; ++c) o[c] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
 };
 
@@ -64,6 +101,16 @@ __device__ __forceinline__ u32x4 load16(const uint16_t* p) {
 // streaming rate of the full and sparse layers by 5-20 % over ordinary loads.
 __device__ __forceinline__ u32x4 load16_stream(const uint16_t* p) {
   return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
+}
+
+__device__ __forceinline__ u32x2 load8_stream(const uint16_t* p) {
+  return __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(p));
+}
+// A lane's V columns of one row: D/16 bf16.
+template <int D>
+__device__ __forceinline__ auto load_v_stream(const uint16_t* p) {
+  if constexpr (D == 128) return load16_stream(p);
+  else return load8_stream(p);
 }
 
 __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
@@ -82,115 +129,167 @@ __device__ __forceinline__ void wave_lds_sync() {
 }
 
 // The query operand of the MFMA: the G query vectors of KV head g (row `qrow` = b*Hq + g*G of
-// q), lane (quad, hcol) holding 8 head-dim values of head hcol; columns hcol >= G are zero.
+// q), lane (quad, hcol) holding 8 head-dim values of head hcol % S; columns of no head are zero.
 template <int D, int G>
 __device__ __forceinline__ void load_query(bf16x8 (&qb)[Geo<D>::NK], const uint16_t* q,
                                            size_t qrow, int lane) {
-  const int quad = lane >> 4, hcol = lane & 15;
-  const uint16_t* qp = q + (qrow + min(hcol, G - 1)) * D + 8 * quad;
+  const int quad = lane >> 4, head = (lane & 15) % kCopy<G>;
+  const uint16_t* qp = q + (qrow + min(head, G - 1)) * D + 8 * quad;
 #pragma unroll
   for (int ks = 0; ks < Geo<D>::NK; ++ks) {
     u32x4 w = load16(qp + 32 * ks);
-    if (hcol >= G) w = u32x4{0u, 0u, 0u, 0u};
+    if (head >= G) w = u32x4{0u, 0u, 0u, 0u};
     qb[ks] = __builtin_bit_cast(bf16x8, w);
   }
 }
 
-// Loads the [16, D] K and V tile that starts at kt / vt (one page of one KV head).  With
+template <int D>
+__device__ __forceinline__ int k_row(int i, int lane) { return Geo<D>::RPL * i + lane / Geo<D>::CPR; }
+
+// Loads the [16, D] K and V tile that starts at kt / vt (one page of one KV head; both
+// wave-uniform, so that a load is a scalar base, one lane offset and an immediate).  With
 // real == false the loads are still issued, so that a loop's memory waits stay uniform, but
-// with every lane at the tile's first 16 bytes: one cache line per load instruction.
+// every lane reads its load's first 16 bytes: one cache line per load instruction.
 template <int D>
 __device__ __forceinline__ void load_page_tile(Tile<D>& t, const uint16_t* kt, const uint16_t* vt,
                                                bool real, int lane) {
   using Gm = Geo<D>;
   const int quad = lane >> 4, hcol = lane & 15;
-  const uint16_t* kp = kt + (real ? (size_t)hcol * D + 8 * quad : 0);
+  const uint32_t ko = real ? 8u * lane : 0u, vo = real ? (uint32_t)(quad * 4 * D + Gm::NC * hcol) : 0u;
 #pragma unroll
-  for (int ks = 0; ks < Gm::NK; ++ks) t.k[ks] = load16_stream(kp + (real ? 32 * ks : 0));
-  const uint16_t* vp = vt + (real ? (size_t)(lane / Gm::LPR) * D + 8 * (lane % Gm::LPR) : 0);
+  for (int i = 0; i < Gm::NK; ++i) t.k[i] = load16_stream(kt + 512 * i + ko);
 #pragma unroll
-  for (int i = 0; i < Gm::NI; ++i) t.v[i] = load16_stream(vp + (real ? (size_t)Gm::RPI * i * D : 0));
+  for (int i = 0; i < 4; ++i) t.v[i] = load_v_stream<D>(vt + D * i + vo);
 }
 
-// Folds one tile's score tile (acc: lane (quad, hcol) holds q_hcol . k_r for rows
-// r = 4*quad .. 4*quad+3, unscaled) into the wave's softmax state.  lp: the wave's LDS slice
-// (16 x 8 + 8 floats).  With LOGITS, the tile's scaled log2-domain logits go to
-// logit_slot[head][16] (LDS).
-template <int D, int G, bool LOGITS>
-__device__ __forceinline__ void fold_tile(const f32x4 acc, const Tile<D>& t, float scale_log2,
-                                          WaveSoftmax<G>& st, float* lp, float* logit_slot,
+// 16-byte piece c of row r of a K tile in the wave's LDS slice (16 * D bf16): the pieces of a row
+// are permuted by the row, so that 16 lanes reading the same piece of 16 rows touch all 64 banks
+// (d = 128: 256-byte rows; d = 64: two rows per 256 bytes).
+template <int D>
+__device__ __forceinline__ int k_slot(int r, int c) {
+  return r * D + 8 * (c ^ (D == 128 ? r : (r >> 1) & 7));
+}
+
+// The A operand of QK^T: lane (quad, m) gets pieces 4*ks + quad of row m.
+template <int D>
+__device__ __forceinline__ void k_operand(const Tile<D>& t, uint16_t* lk, u32x4 (&ka)[Geo<D>::NK],
                                           int lane) {
   using Gm = Geo<D>;
-  const int quad = lane >> 4, hcol = lane & 15;
-  float x[4];
+  wave_lds_sync();
 #pragma unroll
-  for (int r = 0; r < 4; ++r)
-    x[r] = ((t.kmask >> (4 * quad + r)) & 1u) ? acc[r] * scale_log2 : kNegInfF;
+  for (int i = 0; i < Gm::NK; ++i)
+    *reinterpret_cast<u32x4*>(lk + k_slot<D>(k_row<D>(i, lane), lane % Gm::CPR)) = t.k[i];
+  wave_lds_sync();
+#pragma unroll
+  for (int ks = 0; ks < Gm::NK; ++ks)
+    ka[ks] = *reinterpret_cast<const u32x4*>(lk + k_slot<D>(lane & 15, 4 * ks + (lane >> 4)));
+}
+
+// A score may exceed the maximum in use by 2^kRaise before the maximum is raised.
+constexpr float kRaise = 8.f;
+
+// Folds one tile's score tile (acc: lane (quad, hcol) holds q_(hcol % S) . k_r for rows
+// r = 4*quad .. 4*quad+3, unscaled) into the wave's softmax state.  With LOGITS, the tile's
+// scaled log2-domain logits go to logit_slot[head][16] (LDS).
+template <int D, int G, bool LOGITS>
+__device__ __forceinline__ void fold_tile(f32x4 acc, Tile<D>& t, float scale_log2,
+                                          WaveSoftmax<D, G>& st, float* logit_slot, int lane) {
+  using Gm = Geo<D>;
+  constexpr int S = kCopy<G>;
+  const int quad = lane >> 4, hcol = lane & 15;
+  const uint32_t kmask = __builtin_amdgcn_readfirstlane(t.kmask);
+  if (kmask != 0xffffu) {   // rows past the end (their K and V may hold NaN)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const bool ok = (kmask >> (4 * quad + r)) & 1u;
+      acc[r] = ok ? acc[r] : kNegInfF;
+#pragma unroll
+      for (int w = 0; w < Gm::NW; ++w) t.v[r][w] = ok ? t.v[r][w] : 0u;
+    }
+  }
   if (LOGITS && hcol < G)
-    *reinterpret_cast<f32x4*>(logit_slot + hcol * 16 + 4 * quad) = f32x4{x[0], x[1], x[2], x[3]};
-  float mx = fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]));
-  mx = max_xor32(max_xor16(mx));
-  const float m_new = fmaxf(st.m_run, mx);
-  // m_new is finite whenever the tile has a valid row (always, for valid selections); the
-  // guard keeps an all-masked tile from turning the running state into NaN
-  const float m_use = (m_new == kNegInfF) ? 0.f : m_new;
-  const float alpha = exp2f(st.m_run - m_use);
-  float p[4], ps = 0.f;
+    *reinterpret_cast<f32x4*>(logit_slot + hcol * 16 + 4 * quad) = acc * scale_log2;
+
+  float m_use = st.m_run;
+  const float mx = fmaxf(fmaxf(acc[0], acc[1]), fmaxf(acc[2], acc[3]));
+  // negated, so that a maximum of -inf (nothing folded in yet: inf, or NaN where the tile's
+  // scores are -inf too) and NaN scores take the branch
+  if (__any(!(fmaf(mx, scale_log2, -m_use) <= kRaise))) {
+    const float m_new = fmaxf(st.m_run, max_xor32(max_xor16(mx)) * scale_log2);
+    m_use = (m_new == kNegInfF) ? 0.f : m_new;
+    const float alpha = exp2f(st.m_run - m_use);
+    st.m_run = m_new;
+    st.l_run *= alpha;
+    // the factor of output row 4*quad + r, from a lane of its head
+    float row[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float lo = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(alpha), r));
+      const float hi = S == 8 ? __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(alpha), 4 + r)) : lo;
+      row[r] = (quad & 1) ? hi : lo;
+    }
+#pragma unroll
+    for (int c = 0; c < Gm::NC; ++c)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) st.o[c][r] *= row[r];
+  }
+  float p[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) p[r] = __builtin_amdgcn_exp2f(fmaf(acc[r], scale_log2, -m_use));
+  st.l_run += (p[0] + p[1]) + (p[2] + p[3]);
+
+  // The term of the probabilities that this lane's copy of the head carries: p less the upper
+  // parts that the lower copies carry.  (With S = 4 the fourth copy carries a third term again;
+  // its output rows are dropped in the end.)
+  constexpr uint32_t kHigh = 0xffff0000u;
+  const uint32_t m1 = hcol >= S ? kHigh : 0u, m2 = hcol >= 2 * S ? kHigh : 0u;
+  auto less_high = [](float x, uint32_t m) { return x - __uint_as_float(__float_as_uint(x) & m); };
+  auto pack = [](float lo, float hi) {   // the upper halves of two floats
+    return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
+  };
+  float a1[4];
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    p[r] = exp2f(x[r] - m_use);
-    ps += p[r];
+    a1[r] = less_high(p[r], m1);
+    if (S == 4) a1[r] = less_high(a1[r], m2);
   }
-  ps = sum_xor32(sum_xor16(ps));
-  st.l_run = st.l_run * alpha + ps;
-  st.m_run = m_new;
-
-  wave_lds_sync();
-  if (hcol < G) {
+  const u32x2 pa = {pack(a1[0], a1[1]), pack(a1[2], a1[3])};
+  u32x2 pb = {0u, 0u};
+  if (S == 8) {   // the third term, from the second copies; the first copies' rows get nothing
+    float a2[4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) lp[(4 * quad + r) * 8 + hcol] = p[r];
-    if (quad == 0) lp[128 + hcol] = alpha;
-  }
-  wave_lds_sync();
-
-#pragma unroll
-  for (int h = 0; h < G; ++h) {
-    const float al = lp[128 + h];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) st.o[h][e] *= al;
+    for (int r = 0; r < 4; ++r) a2[r] = less_high(a1[r], kHigh);
+    pb = u32x2{pack(a2[0], a2[1]), pack(a2[2], a2[3])};
+    pb[0] &= hcol >= S ? 0xffffffffu : 0u;
+    pb[1] &= hcol >= S ? 0xffffffffu : 0u;
   }
 #pragma unroll
-  for (int i = 0; i < Gm::NI; ++i) {
-    const int row = Gm::RPI * i + lane / Gm::LPR;
-    u32x4 w = t.v[i];
-    if (!((t.kmask >> row) & 1u)) w = u32x4{0u, 0u, 0u, 0u};   // rows past the end may hold NaN
-    float v[8];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      v[2 * c] = __uint_as_float(w[c] << 16);
-      v[2 * c + 1] = __uint_as_float(w[c] & 0xffff0000u);
-    }
-    const float* pr = lp + row * 8;
-#pragma unroll
-    for (int h = 0; h < G; ++h) {
-      const float ph = pr[h];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) st.o[h][e] = fmaf(ph, v[e], st.o[h][e]);
-    }
+  for (int c = 0; c < Gm::NC; ++c) {
+    const uint32_t pick = (c & 1) ? 0x07060302u : 0x05040100u;
+    const int w = c / 2;
+    const u32x2 vb = {__builtin_amdgcn_perm(t.v[1][w], t.v[0][w], pick),
+                      __builtin_amdgcn_perm(t.v[3][w], t.v[2][w], pick)};
+    st.o[c] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(i16x4, pa),
+                                                        __builtin_bit_cast(i16x4, vb), st.o[c], 0, 0, 0);
+    if (S == 8)
+      st.o[c] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(i16x4, pb),
+                                                          __builtin_bit_cast(i16x4, vb), st.o[c], 0, 0, 0);
   }
 }
 
 // Folds one tile into the wave's softmax state, QK^T on the matrix cores (see the file header).
 template <int D, int G, bool LOGITS>
-__device__ __forceinline__ void process_tile(const Tile<D>& t, const bf16x8 (&qb)[Geo<D>::NK],
-                                             float scale_log2, WaveSoftmax<G>& st, float* lp,
-                                             float* logit_slot, int lane) {
+__device__ __forceinline__ void process_tile(Tile<D>& t, const bf16x8 (&qb)[Geo<D>::NK],
+                                             float scale_log2, WaveSoftmax<D, G>& st,
+                                             uint16_t* lk, float* logit_slot, int lane) {
+  u32x4 ka[Geo<D>::NK];
+  k_operand<D>(t, lk, ka, lane);
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int ks = 0; ks < Geo<D>::NK; ++ks)
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, t.k[ks]), qb[ks],
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ka[ks]), qb[ks],
                                                   acc, 0, 0, 0);
-  fold_tile<D, G, LOGITS>(acc, t, scale_log2, st, lp, logit_slot, lane);
+  fold_tile<D, G, LOGITS>(acc, t, scale_log2, st, logit_slot, lane);
 }
 
 // The same score tile with QK^T on the vector ALUs, a build option (DELTA_QK_VALU) kept for
@@ -211,16 +310,18 @@ __device__ __forceinline__ void stage_query_lds(const bf16x8 (&qb)[Geo<D>::NK], 
 }
 
 template <int D, int G, bool LOGITS>
-__device__ __forceinline__ void process_tile_valu(const Tile<D>& t, const uint16_t* sq,
-                                                  float scale_log2, WaveSoftmax<G>& st, float* lp,
-                                                  float* logit_slot, int lane) {
+__device__ __forceinline__ void process_tile_valu(Tile<D>& t, const uint16_t* sq,
+                                                  float scale_log2, WaveSoftmax<D, G>& st, float* lp,
+                                                  uint16_t* lk, float* logit_slot, int lane) {
   const int quad = lane >> 4, r = lane & 15;
+  u32x4 ka[Geo<D>::NK];
+  k_operand<D>(t, lk, ka, lane);
   float part[G];
 #pragma unroll
   for (int h = 0; h < G; ++h) part[h] = 0.f;
 #pragma unroll
   for (int ks = 0; ks < Geo<D>::NK; ++ks) {
-    const u32x4 kw = t.k[ks];
+    const u32x4 kw = ka[ks];
 #pragma unroll
     for (int h = 0; h < G; ++h) {
       const u32x4 qw = *reinterpret_cast<const u32x4*>(sq + h * D + 32 * ks + 8 * quad);
@@ -243,21 +344,23 @@ __device__ __forceinline__ void process_tile_valu(const Tile<D>& t, const uint16
   wave_lds_sync();
   f32x4 acc;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) acc[i] = r < G ? lp[(4 * quad + i) * 8 + r] : 0.f;
-  fold_tile<D, G, LOGITS>(acc, t, scale_log2, st, lp, logit_slot, lane);
+  for (int i = 0; i < 4; ++i) acc[i] = r % kCopy<G> < G ? lp[(4 * quad + i) * 8 + r % kCopy<G>] : 0.f;
+  fold_tile<D, G, LOGITS>(acc, t, scale_log2, st, logit_slot, lane);
 }
 
-// Sums each lane's output share over the lanes that hold the same head-dim columns: afterwards
-// lanes 0 .. LPR-1 hold the wave's complete outputs o[h][8*lane .. 8*lane+7].
+// The wave's complete sums and outputs: afterwards every lane holds the sum of head hcol % S in
+// l_run, and lane (quad, n) with quad < S / 4 the outputs o[c][r] of head 4*quad + r (< G),
+// head-dim column NC*n + c.  Adds the rows of the copies of a head (its terms).
 template <int D, int G>
-__device__ __forceinline__ void reduce_outputs(WaveSoftmax<G>& st) {
+__device__ __forceinline__ void reduce_outputs(WaveSoftmax<D, G>& st, int lane) {
+  st.l_run = sum_xor32(sum_xor16(st.l_run));
 #pragma unroll
-  for (int h = 0; h < G; ++h)
+  for (int c = 0; c < Geo<D>::NC; ++c)
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      float v = st.o[h][e];
-      if (Geo<D>::LPR == 8) v += lane_xor8(v);
-      st.o[h][e] = sum_xor32(sum_xor16(v));
+    for (int r = 0; r < 4; ++r) {
+      float v = st.o[c][r];
+      if (kCopy<G> == 4) v = sum_xor16(lane < 48 ? v : 0.f);
+      st.o[c][r] = sum_xor32(v);
     }
 }
 

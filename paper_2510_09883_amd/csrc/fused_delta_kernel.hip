@@ -66,14 +66,13 @@ __global__ __launch_bounds__(kAttnThreads) void fused_delta_kernel(const FusedAr
   const int np = min(kC, n_pages - p0);
 
   __shared__ int s_pages[kC];
-  __shared__ float s_p[kWaves][16 * 8 + 8];
+  __shared__ __attribute__((aligned(16))) uint16_t s_k[kWaves][16 * D];   // a wave's K tile
   __shared__ __attribute__((aligned(16))) float s_logit[kFusedMaxQHeads * kC * 16];
   __shared__ float s_M[kFusedMaxQHeads], s_L[kFusedMaxQHeads], s_lse[kFusedMaxQHeads];
   __shared__ int s_last;
   if (tid < np) s_pages[tid] = checked_page(a.page_table[(size_t)b * a.max_pages + p0 + tid], a.n_pages, a.status);
   if (DELTA_DEBUG && c == 0 && tid == 0 && (a.seq_lens[b] < 1 || a.seq_lens[b] > a.max_seq_len))
     debug_flag(a.status, DELTA_DEBUG_SEQ_LEN);
-  float* lp = s_p[wave];
 
   const size_t part_rows = (size_t)gridDim.y * Hkv * a.n_chunks * G;   // rows of G x D / G x 2
   const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(
@@ -86,7 +85,7 @@ __global__ __launch_bounds__(kAttnThreads) void fused_delta_kernel(const FusedAr
   for (int g = wave; g < Hkv; g += kWaves) {   // wave-uniform
     bf16x8 qb[Gm::NK];
     load_query<D, G>(qb, a.q, (size_t)b * Hq + g * G, lane);
-    WaveSoftmax<G> st;
+    WaveSoftmax<D, G> st;
     st.init();
     const size_t head_off = (size_t)g * 16 * D;
     float* lg = s_logit + (size_t)g * kC * G * 16;
@@ -96,7 +95,9 @@ __global__ __launch_bounds__(kAttnThreads) void fused_delta_kernel(const FusedAr
       const size_t page = (size_t)s_pages[kk] * a.page_stride + head_off;
       const int nrows = min(16, s_b - 16 * (p0 + kk));
       t.kmask = (nrows >= 16) ? 0xffffu : ((1u << max(nrows, 0)) - 1u);
+      __builtin_amdgcn_sched_barrier(0);   // loads of different tiles stay in order
       load_page_tile<D>(t, a.k_cache + page, a.v_cache + page, k < np, lane);
+      __builtin_amdgcn_sched_barrier(0);
     };
     Tile<D> t[R];
 #pragma unroll
@@ -106,25 +107,26 @@ __global__ __launch_bounds__(kAttnThreads) void fused_delta_kernel(const FusedAr
       for (int r = 0; r < R; ++r) {
         fetch(t[(r + R - 1) % R], k + r + R - 1);
         if (k + r < np)
-          process_tile<D, G, true>(t[r], qb, a.scale_log2, st, lp, lg + (k + r) * G * 16, lane);
+          process_tile<D, G, true>(t[r], qb, a.scale_log2, st, s_k[wave],
+                                    lg + (k + r) * G * 16, lane);
       }
     }
-    reduce_outputs<D, G>(st);
+    reduce_outputs<D, G>(st, lane);
     const int prow = (((b * Hkv + g) * a.n_chunks) + c) * G;   // partial row of head 0
     if (quad == 0 && hcol < G)
       __builtin_amdgcn_raw_buffer_store_b64(
           __builtin_bit_cast(u32x2, make_float2(st.m_run, st.l_run)), rml, (prow + hcol) * 8, 0,
           kCoherent);
-    if (lane < Gm::LPR) {
+    if (quad < kCopy<G> / 4) {
 #pragma unroll
-      for (int h = 0; h < G; ++h) {
-        const int off = ((prow + h) * D + 8 * lane) * 4;
-        __builtin_amdgcn_raw_buffer_store_b128(
-            __builtin_bit_cast(u32x4, f32x4{st.o[h][0], st.o[h][1], st.o[h][2], st.o[h][3]}), ro,
-            off, 0, kCoherent);
-        __builtin_amdgcn_raw_buffer_store_b128(
-            __builtin_bit_cast(u32x4, f32x4{st.o[h][4], st.o[h][5], st.o[h][6], st.o[h][7]}), ro,
-            off + 16, 0, kCoherent);
+      for (int r = 0; r < 4; ++r) {
+        if (4 * quad + r >= G) break;
+        const int off = ((prow + 4 * quad + r) * D + Gm::NC * hcol) * 4;
+#pragma unroll
+        for (int c = 0; c < Gm::NC; c += 4)
+          __builtin_amdgcn_raw_buffer_store_b128(
+              __builtin_bit_cast(u32x4, f32x4{st.o[c][r], st.o[c + 1][r], st.o[c + 2][r], st.o[c + 3][r]}),
+              ro, off + 4 * c, 0, kCoherent);
       }
     }
   }

@@ -1,0 +1,63 @@
+"""GPU parity of the attention tile step (both contractions on the matrix cores, lazily raised
+softmax maximum) where it can go wrong: scores that grow from tile to tile (the maximum is raised
+again and again), shrink, or jump late by hundreds of binary orders, every padding of the query
+heads into the score tile's columns, both head dims, and tails of one to sixteen rows.
+
+Tolerance: a bf16 output is off by at most 2^-9 of its value, and an fp32 logit of up to 2^9
+(log2 domain) by a few 2^-15, i.e. a weight by some 1e-4 of itself; with |v| <= 4 that leaves
+|o - o_ref| <= 2^-8 |o_ref| + 2e-3.
+"""
+import numpy as np
+import pytest
+import torch
+
+from gpu_helpers import D
+from oracle import delta_oracle as O
+from paper_2510_09883_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+LENS = [1, 15, 16, 17, 64, 83, 305]
+
+
+def _pattern(kind, s, d, g):
+    """Keys [s, d] whose scores against a query of ones follow `kind`."""
+    t = torch.arange(s, dtype=torch.float32)
+    level = {"rising": 0.05 * t, "falling": -0.05 * t, "spike": torch.where(t == s - 1, 30.0, -2.0),
+             "flat": 0 * t, "steps": 8.0 * (t // 16 % 3)}[kind]
+    return level[:, None] + 0.1 * torch.randn((s, d), generator=g)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("G", [1, 3, 4, 5, 8])
+def test_tile_step_matches_float64(G, d):
+    dd, hkv = D(), 2
+    hq = hkv * G
+    g = torch.Generator().manual_seed(100 * G + d)
+    for kind in ("rising", "falling", "spike", "flat", "steps"):
+        n = [(s + 15) // 16 for s in LENS]
+        pt = torch.zeros((len(LENS), max(n)), dtype=torch.int32)
+        k = torch.full((sum(n), hkv, 16, d), float("nan"), dtype=torch.bfloat16)
+        v = torch.full_like(k, float("nan"))     # rows past a sequence's end stay NaN
+        off = 0
+        for b, s in enumerate(LENS):
+            pt[b, :n[b]] = torch.arange(off, off + n[b])
+            for h in range(hkv):
+                for cache, x in ((k, _pattern(kind, s, d, g)),
+                                 (v, torch.randn((s, d), generator=g).clamp(-4, 4))):
+                    rows = torch.full((16 * n[b], d), float("nan"), dtype=torch.bfloat16)
+                    rows[:s] = x.to(torch.bfloat16)
+                    cache[off:off + n[b], h] = rows.view(-1, 16, d)
+            off += n[b]
+        q = (1 + 0.3 * torch.randn((len(LENS), hq, d), generator=g)).to(torch.bfloat16)
+        shape = dd.make_shape(len(LENS), hq, hkv, d, max(n), max(LENS))
+        dev = [x.cuda() for x in (k, v, pt, torch.tensor(LENS, dtype=torch.int32), q)]
+        out = torch.full_like(dev[4], float("nan"))
+        dd.delta_full_attn(shape, dd.make_kv(*dev[:4]), dev[4], out, dd.alloc_workspace(shape))
+        torch.cuda.synchronize()
+        for b, s in enumerate(LENS):
+            K = O.gather_tokens(synth.bits(k), pt[b].numpy(), s)
+            V = O.gather_tokens(synth.bits(v), pt[b].numpy(), s)
+            o, _ = O.full_attention(O.bf16_bits_to_f64(synth.bits(q[b])), K, V, O.default_scale(d))
+            err = np.abs(out[b].float().cpu().numpy() - o) - (2.0 ** -8 * np.abs(o) + 2e-3)
+            assert err.max() <= 0, f"{kind} G {G} d {d} length {s}: over tolerance by {err.max():.3g}"
