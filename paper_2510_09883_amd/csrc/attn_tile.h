@@ -146,20 +146,38 @@ __device__ __forceinline__ void load_query(bf16x8 (&qb)[Geo<D>::NK], const uint1
 template <int D>
 __device__ __forceinline__ int k_row(int i, int lane) { return Geo<D>::RPL * i + lane / Geo<D>::CPR; }
 
+// Buffer-resource word 3 for raw (unformatted, stride 0) buffer access on gfx950, and the
+// cache-policy operand of the buffer builtins for non-temporal loads.
+constexpr int kRawBufferFlags = 0x00020000;
+constexpr int kNonTemporal = 2;
+
 // Loads the [16, D] K and V tile that starts at kt / vt (one page of one KV head; both
-// wave-uniform, so that a load is a scalar base, one lane offset and an immediate).  With
-// real == false the loads are still issued, so that a loop's memory waits stay uniform, but
-// every lane reads its load's first 16 bytes: one cache line per load instruction.
+// wave-uniform).  With real == false the loads are still issued, so that a loop's memory waits
+// stay uniform, but from an empty buffer: they return zeros and read nothing.  (Buffer loads: the
+// address is a scalar descriptor and a lane offset that no tile changes.  With global loads the
+// compiler sometimes formed 64-bit lane addresses in registers of tiles still in flight, whose
+// loads it then waited for.)
 template <int D>
 __device__ __forceinline__ void load_page_tile(Tile<D>& t, const uint16_t* kt, const uint16_t* vt,
                                                bool real, int lane) {
   using Gm = Geo<D>;
   const int quad = lane >> 4, hcol = lane & 15;
-  const uint32_t ko = real ? 8u * lane : 0u, vo = real ? (uint32_t)(quad * 4 * D + Gm::NC * hcol) : 0u;
+  const int bytes = real ? 16 * D * 2 : 0;
+  const __amdgpu_buffer_rsrc_t rk =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(kt), 0, bytes, kRawBufferFlags);
+  const __amdgpu_buffer_rsrc_t rv =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(vt), 0, bytes, kRawBufferFlags);
+  const int ko = 16 * lane, vo = 2 * (quad * 4 * D + Gm::NC * hcol);
 #pragma unroll
-  for (int i = 0; i < Gm::NK; ++i) t.k[i] = load16_stream(kt + 512 * i + ko);
+  for (int i = 0; i < Gm::NK; ++i)
+    t.k[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rk, ko + 1024 * i, 0, kNonTemporal));
 #pragma unroll
-  for (int i = 0; i < 4; ++i) t.v[i] = load_v_stream<D>(vt + D * i + vo);
+  for (int i = 0; i < 4; ++i) {
+    if constexpr (D == 128)
+      t.v[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rv, vo + 2 * D * i, 0, kNonTemporal));
+    else
+      t.v[i] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(rv, vo + 2 * D * i, 0, kNonTemporal));
+  }
 }
 
 // 16-byte piece c of row r of a K tile in the wave's LDS slice (16 * D bf16): the pieces of a row
@@ -348,20 +366,45 @@ __device__ __forceinline__ void process_tile_valu(Tile<D>& t, const uint16_t* sq
   fold_tile<D, G, LOGITS>(acc, t, scale_log2, st, logit_slot, lane);
 }
 
+template <int W>
+struct FloatVec { typedef float type __attribute__((ext_vector_type(W))); };
+template <>
+struct FloatVec<1> { typedef float type; };
+
 // The wave's complete sums and outputs: afterwards every lane holds the sum of head hcol % S in
-// l_run, and lane (quad, n) with quad < S / 4 the outputs o[c][r] of head 4*quad + r (< G),
-// head-dim column NC*n + c.  Adds the rows of the copies of a head (its terms).
-template <int D, int G>
-__device__ __forceinline__ void reduce_outputs(WaveSoftmax<D, G>& st, int lane) {
+// l_run, and emit(head, column, w consecutive outputs) has been called for every output of the G
+// heads, each by one lane.  The rows that belong to one head (its terms) stand in different
+// 16-lane rows of the wave; a swap of two registers' halves brings two sums' addends together
+// at once, so adding and spreading them over the lanes takes NC*4 swaps and adds in all.
+template <int D, int G, class F>
+__device__ __forceinline__ void reduce_outputs(WaveSoftmax<D, G>& st, int lane, F&& emit) {
+  constexpr int NC = Geo<D>::NC, S = kCopy<G>;
+  const int quad = lane >> 4, hcol = lane & 15;
   st.l_run = sum_xor32(sum_xor16(st.l_run));
+  float h[NC / 2][4];   // lanes 0-31: columns c < NC/2, lanes 32-63: columns c + NC/2
 #pragma unroll
-  for (int c = 0; c < Geo<D>::NC; ++c)
+  for (int c = 0; c < NC / 2; ++c)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      float v = st.o[c][r];
-      if (kCopy<G> == 4) v = sum_xor16(lane < 48 ? v : 0.f);
-      st.o[c][r] = sum_xor32(v);
+      float x = st.o[c][r], y = st.o[c + NC / 2][r];
+      if (S == 4) {   // the fourth copy repeats the third term
+        x = lane < 48 ? x : 0.f;
+        y = lane < 48 ? y : 0.f;
+      }
+      h[c][r] = sum_swap32(x, y);
     }
+  constexpr int W = S == 4 ? NC / 4 : NC / 2;
+  const int col = NC * hcol + (quad >> 1) * (NC / 2) + (S == 4 ? (quad & 1) * (NC / 4) : 0);
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int head = S == 4 ? r : 4 * (quad & 1) + r;
+    typename FloatVec<W>::type v;
+    float e[W];
+#pragma unroll
+    for (int j = 0; j < W; ++j) e[j] = S == 4 ? sum_swap16(h[j][r], h[j + NC / 4][r]) : h[j][r];
+    __builtin_memcpy(&v, e, sizeof(v));
+    if (head < G) emit(head, col, v);
+  }
 }
 
 }  // namespace delta

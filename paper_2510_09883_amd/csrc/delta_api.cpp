@@ -53,29 +53,34 @@ int min_groups_per_split() {
 }
 
 // Most splits per (sequence, kv head).  The last workgroup's merge reads every split's partial
-// (one batch of loads per 16 splits) and each split adds an arrival on the same counter, so
-// beyond ~16 splits the combine costs more than the shorter loop saves (measured on MI355X with
-// one sequence of 8K tokens).  DELTA_ATTN_MAX_SPLITS overrides it for tuning.
-int max_splits() {
+// and each split adds an arrival on the same counter, so beyond ~16 splits the combine costs
+// more than the shorter loop saves where the pairs fill the device anyway; with fewer than 32
+// pairs (256 workgroups at 8 splits each and more) the splits are what fills it, up to 32.  Measured
+// on MI355X with 16 and 32 splits: one 32K sequence with 4 KV heads 26.9 and 22.0 us, one 128K
+// sequence with 8 KV heads 103.7 and 89.2; 64 splits gave 22.8 and 91.4.  DELTA_ATTN_MAX_SPLITS
+// overrides it for tuning.
+int max_splits(int pairs) {
   static int v = [] {
     const char* e = getenv("DELTA_ATTN_MAX_SPLITS");
     int x = e ? atoi(e) : 0;
-    return x > 0 ? std::min(x, kMaxSplits) : 16;
+    return std::max(0, std::min(x, kMaxSplits - 1));
   }();
-  return v;
+  return v > 0 ? v : pairs < 32 ? 32 : 16;
 }
 
 struct SplitPlan {
   int n_split = 0;
   int gps = 0;
   int max_groups = 0;
-  int slots = 0;       // partial slots per (sequence, kv head)
-  int chunk_min = 0;   // balanced decomposition: shortest run
-  int balance = 0;     // balanced decomposition allowed (dense launches)
+  int slots = 0;         // partial slots per (sequence, kv head)
+  int slots16 = 0;       // the same with at most 16 splits (see Layout::total16)
+  int n_runs = 0;        // balanced decomposition: runs (0: not taken)
+  int chunk_min = 0;     // balanced decomposition: shortest run
+  int static_rounds = 1; // static pieces that a CU takes one after another
 };
 
-// Whether dense launches may spread a ragged batch's work evenly (the balanced decomposition
-// of the attention kernel).  DELTA_ATTN_BALANCE=0 keeps the static one, for comparison.
+// Whether launches may spread a batch's work evenly (the balanced decomposition of the attention
+// kernel).  DELTA_ATTN_BALANCE=0 keeps the static one, for comparison.
 bool balance_enabled() {
   static int v = [] {
     const char* e = getenv("DELTA_ATTN_BALANCE");
@@ -85,44 +90,63 @@ bool balance_enabled() {
 }
 
 // Splits per (sequence, kv head) and groups per split for a launch over at most `max_groups`
-// groups of 16 rows.  Deterministic in the shape, so a FULL and a DELTA call over the same
-// shape use the same plan (and give bitwise-identical outputs).
-bool plan_split(int pairs, int max_groups, int slot_cap, SplitPlan* p) {
+// groups of 16 rows, and the balanced decomposition's runs.  Deterministic in the shape, so a
+// FULL and a DELTA call over the same shape use the same plan (and give bitwise-identical
+// outputs).  `dense` is null for full and Delta layers; a sparse layer's groups are its
+// selection's budget, which most sequences have in full, so the host can tell whether the
+// static pieces fill the device evenly, and it shares the dense layers' partial slots.
+bool plan_split(int batch, int pairs, int max_groups, int slot_cap, const SplitPlan* dense,
+                SplitPlan* p) {
   if (max_groups < 1) max_groups = 1;
-  int want = std::max(1, ceil_div(target_workgroups(), pairs));
-  int most = std::max(1, ceil_div(max_groups, min_groups_per_split()));
-  int n_split = std::min(std::min(want, most), max_splits());
-  int gps = ceil_div(max_groups, n_split);
-  if (gps > slot_cap) gps = slot_cap;
-  n_split = ceil_div(max_groups, gps);
-  if (n_split > kMaxSplits) return false;
-  p->n_split = n_split;
-  p->gps = gps;
+  if (ceil_div(max_groups, slot_cap) > kMaxSplits) return false;
+  const int target = target_workgroups();
+  const int want = std::max(1, ceil_div(target, pairs));
+  const int most = std::max(1, ceil_div(max_groups, min_groups_per_split()));
+  const int cap = max_splits(pairs);
+  auto splits = [&](int limit, int longest) {
+    const int n = std::min(std::min(want, most), limit);
+    return ceil_div(max_groups, std::min(ceil_div(max_groups, n), longest));
+  };
+  p->n_split = splits(cap, max_groups);
+  p->gps = ceil_div(max_groups, p->n_split);
   p->max_groups = max_groups;
-  p->slots = n_split;
-  return true;
-}
+  p->slots = p->n_split;
+  // with at most 16 splits, lists of one piece in LDS at once and one slot more for the pieces of
+  // a ragged batch
+  const int cut16 = std::max(min_groups_per_split(), ceil_div(max_groups, std::min(cap, 16)));
+  p->slots16 = splits(std::min(cap, 16), slot_cap);
+  if (!dense && balance_enabled() && batch >= 2 && batch <= kBalanceMaxBatch && cut16 <= slot_cap)
+    p->slots16 = std::max(p->slots16, ceil_div(max_groups, cut16) + 1);
 
-// The balanced decomposition of a dense launch over `batch` sequences, 2 to kBalanceMaxBatch
-// (one sequence cannot be ragged; the kernel holds one sequence length per lane).  Runs are at
-// least chunk_min groups, so no pair is cut into more than slots pieces, and at most
-// kMaxRowSlots: the run of a workgroup of the static grid, ceil(work / workgroups), never
-// exceeds gps.
-void plan_balance(int batch, int pairs, SplitPlan* p) {
-  const int cap = std::min(max_splits(), kMaxSplits - 1);
-  const int chunk_min = std::max(min_groups_per_split(), ceil_div(p->max_groups, cap));
-  if (!balance_enabled() || batch < 2 || batch > kBalanceMaxBatch || chunk_min > kMaxRowSlots) return;
-  // the kernel does the cut's arithmetic in 32 bits
-  if ((int64_t)pairs * p->max_groups >= ((int64_t)1 << 31)) return;
-  p->chunk_min = chunk_min;
-  p->slots = std::max(p->n_split, ceil_div(p->max_groups, chunk_min) + 1);
-  p->balance = 1;
+  const int64_t wgs = (int64_t)p->n_split * pairs;
+  p->static_rounds = (int)std::min<int64_t>((wgs + target - 1) / target, 1 << 10);
+  // The balanced decomposition, one run for each CU: the kernel holds one sequence length per
+  // lane and does the cut's arithmetic in 32 bits (20 x the work included), and cuts no pair into
+  // more pieces than it has slots.  One sequence with pairs enough has no need of it.
+  const int64_t work = (int64_t)pairs * (max_groups + kPieceCost);
+  if (!balance_enabled() || batch > kBalanceMaxBatch || work >= ((int64_t)1 << 26)) return true;
+  if (batch == 1 && pairs >= 32) return true;
+  const int cut = std::max(min_groups_per_split(), ceil_div(max_groups, cap));
+  int slots = std::max(p->n_split, ceil_div(max_groups, cut) + 1);
+  if (dense) {
+    // (the test that the kernel makes with the actual lengths)
+    const int64_t even = (work + target - 1) / target + kPieceCost;
+    if (20 * even > 19 * (int64_t)(p->gps + kPieceCost) * p->static_rounds) return true;
+    slots = std::max(p->n_split, std::min(slots, dense->slots));
+  }
+  if (slots < 2) return true;
+  p->slots = slots;
+  p->n_runs = (int)std::min<int64_t>(wgs, target);
+  p->chunk_min = min_groups_per_split();
+  return true;
 }
 
 struct Layout {
   size_t status = 0, counters = 0, part_ml = 0, part_o = 0, logits = 0, lse = 0, uscores = 0, phys = 0;
   size_t fcnt = 0, fflag = 0;
   size_t total = 0;
+  size_t total16 = 0;     // total with at most 16 splits: what the allocation-free step's limit is
+                          // on (its scratch has kNoallocSplitBytes more for the others)
   int fused_chunks = 0;   // chunks per sequence of the fused Delta kernel
   int max_split = 0;
   int logit_pages = 0;
@@ -176,21 +200,23 @@ int make_layout(const delta_shape_t* s, const delta_select_t* sel, Layout* L) {
   if (sel && (rc = check_select(sel))) return rc;
   const int pairs = s->batch * s->n_kv_heads;
   const int G = s->n_q_heads / s->n_kv_heads;
-  if (!plan_split(pairs, ceil_div(s->max_seq_len, 16), kMaxRowSlots, &L->dense))
+  if (!plan_split(s->batch, pairs, ceil_div(s->max_seq_len, 16), kMaxRowSlots, nullptr, &L->dense))
     return DELTA_ERR_UNSUPPORTED;
-  plan_balance(s->batch, pairs, &L->dense);
   L->max_split = L->dense.slots;
+  int max_split16 = L->dense.slots16;
   if (sel) {
     const int K = sel->budget_tokens / sel->unit_tokens;
     if (sel->unit_tokens == 16) {
       L->sparse_mode = ROWS_SEL_PAGE;
-      if (!plan_split(pairs, K, kMaxRowSlots, &L->sparse)) return DELTA_ERR_UNSUPPORTED;
+      if (!plan_split(s->batch, pairs, K, kMaxRowSlots, &L->dense, &L->sparse)) return DELTA_ERR_UNSUPPORTED;
     } else {
       L->sparse_mode = ROWS_SEL_TOKEN;
-      if (!plan_split(pairs, ceil_div(K, 16), kMaxRowSlots / 16, &L->sparse))
+      if (!plan_split(s->batch, pairs, ceil_div(K, 16), kMaxRowSlots / 16,
+                      &L->dense, &L->sparse))
         return DELTA_ERR_UNSUPPORTED;
     }
     L->max_split = std::max(L->max_split, L->sparse.slots);
+    max_split16 = std::max(max_split16, L->sparse.slots16);
     // the selection holds the older units of one sequence in one workgroup's registers
     if (ceil_div(s->max_seq_len, sel->unit_tokens) - recent_units_of(sel) > kMaxSelectKeys)
       return DELTA_ERR_UNSUPPORTED;
@@ -201,6 +227,7 @@ int make_layout(const delta_shape_t* s, const delta_select_t* sel, Layout* L) {
   if (sel) {
     L->fused_chunks = ceil_div(L->logit_pages, kFusedChunkPages);
     part_splits = std::max(part_splits, L->fused_chunks);
+    max_split16 = std::max(max_split16, L->fused_chunks);
   }
   size_t off = 0;
   L->status = off;    off = align_up(off + sizeof(uint32_t));   // debug builds' status word
@@ -217,6 +244,11 @@ int make_layout(const delta_shape_t* s, const delta_select_t* sel, Layout* L) {
     L->fflag = off;   off = align_up(off + sizeof(int32_t) * (size_t)s->batch * L->fused_chunks);
   }
   L->total = off;
+  auto part_bytes = [&](int splits) {
+    return align_up(sizeof(float) * (size_t)pairs * splits * G * 2) +
+           align_up(sizeof(float) * (size_t)pairs * splits * G * s->head_dim);
+  };
+  L->total16 = L->total - part_bytes(part_splits) + part_bytes(max_split16);
   return DELTA_OK;
 }
 
@@ -252,8 +284,9 @@ AttnArgs base_args(const delta_shape_t* s, const delta_kv_t* kv, const void* q, 
   a.gps = plan.gps;
   a.max_groups = plan.max_groups;
   a.slots = plan.slots;
+  a.n_runs = plan.n_runs;
   a.chunk_min = plan.chunk_min;
-  a.balance = plan.balance;
+  a.static_rounds = plan.static_rounds;
   a.scale_log2 = scale_log2(s);
   a.n_pages = kv->n_pages;
   a.max_seq_len = s->max_seq_len;
@@ -583,7 +616,9 @@ int delta_decode_step_noalloc(const delta_shape_t* shape, int32_t n_layers, cons
   Layout L;
   int rc = check_step(shape, n_layers, roles, kv, q, out, sel, sel_idx, sel_cnt, &L);
   if (rc) return rc;
-  if (L.total > kNoallocScratchBytes) return DELTA_ERR_WORKSPACE;   // before any device call
+  // (before any device call)
+  if (L.total16 > kNoallocScratchBytes || L.total > kNoallocScratchBytes + kNoallocSplitBytes)
+    return DELTA_ERR_WORKSPACE;
   void* ws = nullptr;
   if (noalloc_scratch(&ws) != hipSuccess) return DELTA_ERR_HIP;
   char* w = static_cast<char*>(ws);

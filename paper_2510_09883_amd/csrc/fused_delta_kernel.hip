@@ -37,7 +37,6 @@ namespace {
 
 constexpr int kWaves = kAttnThreads / 64;
 constexpr int kC = kFusedChunkPages;
-constexpr int kRawBufferFlags = 0x00020000;   // buffer-resource word 3, raw access (gfx950)
 constexpr int kCoherent = 16;                 // device-coherent (sc1) cache policy
 // Bound on the polls of the sequence barrier besides its time limit (each poll is a device
 // round trip plus a short sleep, so this is about a second).
@@ -92,7 +91,7 @@ __global__ __launch_bounds__(kAttnThreads) void fused_delta_kernel(const FusedAr
     // ring of R tiles as in the split kernel; prefetches past the chunk are one-line dummies
     auto fetch = [&](Tile<D>& t, int k) {
       const int kk = min(k, np - 1);
-      const size_t page = (size_t)s_pages[kk] * a.page_stride + head_off;
+      const size_t page = (size_t)__builtin_amdgcn_readfirstlane(s_pages[kk]) * a.page_stride + head_off;
       const int nrows = min(16, s_b - 16 * (p0 + kk));
       t.kmask = (nrows >= 16) ? 0xffffu : ((1u << max(nrows, 0)) - 1u);
       __builtin_amdgcn_sched_barrier(0);   // loads of different tiles stay in order
@@ -111,24 +110,18 @@ __global__ __launch_bounds__(kAttnThreads) void fused_delta_kernel(const FusedAr
                                     lg + (k + r) * G * 16, lane);
       }
     }
-    reduce_outputs<D, G>(st, lane);
     const int prow = (((b * Hkv + g) * a.n_chunks) + c) * G;   // partial row of head 0
+    reduce_outputs<D, G>(st, lane, [&](int head, int col, auto v) {
+      const int off = ((prow + head) * D + col) * 4;
+      if constexpr (sizeof(v) == 16)
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), ro, off, 0, kCoherent);
+      else
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), ro, off, 0, kCoherent);
+    });
     if (quad == 0 && hcol < G)
       __builtin_amdgcn_raw_buffer_store_b64(
           __builtin_bit_cast(u32x2, make_float2(st.m_run, st.l_run)), rml, (prow + hcol) * 8, 0,
           kCoherent);
-    if (quad < kCopy<G> / 4) {
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        if (4 * quad + r >= G) break;
-        const int off = ((prow + 4 * quad + r) * D + Gm::NC * hcol) * 4;
-#pragma unroll
-        for (int c = 0; c < Gm::NC; c += 4)
-          __builtin_amdgcn_raw_buffer_store_b128(
-              __builtin_bit_cast(u32x4, f32x4{st.o[c][r], st.o[c + 1][r], st.o[c + 2][r], st.o[c + 3][r]}),
-              ro, off + 4 * c, 0, kCoherent);
-      }
-    }
   }
 
   // ---- 2. sequence barrier, bounded in time ----------------------------------------------

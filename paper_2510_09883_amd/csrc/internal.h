@@ -23,9 +23,11 @@ enum RowMode {
 };
 
 // Hard limits of the attention kernel's on-chip staging.
-constexpr int kAttnThreads = 256;        // 4 waves of 64
+constexpr int kAttnThreads = 256;        // fused Delta kernel: 4 waves of 64
 constexpr int kMaxSplits = 64;           // split partials combined by the last workgroup
-constexpr int kMaxRowSlots = 1024;       // LDS slots staging a split's page / row list
+constexpr int kMaxRowSlots = 1024;       // LDS slots staging a piece's page / row list
+constexpr int kPieceCost = 8;            // fixed cost of a piece in groups (restaging, ring refill,
+                                         // merge: about 2.5 us, a group 0.3 us of a CU's time)
 constexpr int kMaxGroup = 8;             // query heads per KV head (padded to 16 MFMA columns)
 constexpr int kMaxSelectKeys = 8192;     // candidate units one selection workgroup holds in registers
 constexpr int kBalanceMaxBatch = 64;     // sequences of a balanced dense launch (one per lane)
@@ -54,8 +56,9 @@ struct AttnArgs {
                              // per split; the grid is (n_split, Hkv, B)
   int32_t max_groups;        // host bound on groups per sequence (n_split * gps >= it)
   int32_t slots;             // partial slots per (b, kv head), >= the pieces of any pair
-  int32_t chunk_min;         // shortest run of the balanced decomposition (dense launches)
-  int32_t balance;           // 1: a dense launch may take the balanced decomposition
+  int32_t n_runs;            // runs of the balanced decomposition (<= workgroups); 0: not taken
+  int32_t chunk_min;         // shortest run of the balanced decomposition
+  int32_t static_rounds;     // static pieces that a CU takes one after another
   float scale_log2;          // sm_scale * log2(e)
   int64_t n_pages;           // physical pages of the caches (0: not stated); debug checks
   int32_t max_seq_len;       // host bound of seq_lens[b]; debug checks
@@ -149,6 +152,10 @@ hipError_t launch_fill_zero2(void* p0, size_t bytes0, void* p1, size_t bytes1, h
 // GPU (DELTA_NOALLOC_SCRATCH_BYTES of the C ABI), allocated when the step first runs there.
 // *ptr gets the current device's copy.
 constexpr size_t kNoallocScratchBytes = (size_t)160 << 20;
+// Room beside it for the partials of more than 16 splits (fewer than 32 pairs of at most 8 heads of
+// 128: under 24 x 31 x 8 x 130 floats beyond what 16 splits take), so that the limit on a
+// shape's workspace does not depend on the split plan.
+constexpr size_t kNoallocSplitBytes = (size_t)4 << 20;
 hipError_t noalloc_scratch(void** ptr);
 
 }  // namespace delta

@@ -27,6 +27,17 @@ __device__ __forceinline__ float sum_xor32(float x) {
   return __uint_as_float(p[0]) + __uint_as_float(p[1]);
 }
 
+// Two sums at once: lanes 0-31 get x[l] + x[l + 32], lanes 32-63 y[l - 32] + y[l]; and by rows of
+// 16 lanes, even rows get x[l] + x[l + 16], odd rows y[l - 16] + y[l].
+__device__ __forceinline__ float sum_swap32(float x, float y) {
+  const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+  return __uint_as_float(p[0]) + __uint_as_float(p[1]);
+}
+__device__ __forceinline__ float sum_swap16(float x, float y) {
+  const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+  return __uint_as_float(p[0]) + __uint_as_float(p[1]);
+}
+
 // DPP lane moves inside rows of 16 lanes: x of lane l ^ 1, l ^ 2 (quad permutations) and
 // l ^ 8 (rotation of the row by 8).
 __device__ __forceinline__ float lane_xor1(float x) {
@@ -86,6 +97,8 @@ __device__ __forceinline__ uint32_t wave_min(uint32_t v) {
   const auto q = __builtin_amdgcn_permlane32_swap(v, v, false, false);
   return min(q[0], q[1]);
 }
+
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) { return ~wave_min(~v); }
 
 // Workgroup barrier that orders LDS accesses only: the waves wait for their own LDS operations,
 // not for outstanding global loads (which __syncthreads would also drain), so loads issued

@@ -1,0 +1,144 @@
+"""CPU model of how an attention launch's work is cut (delta_api.cpp plan_split, attn_kernel.hip
+balanced decomposition), checked for the properties the kernel's buffers rely on.
+
+Every (sequence, KV head) pair is COST units of work followed by its 16-row groups; the pairs, in
+(sequence, KV head) order, are cut into runs of equal length, run w for workgroup w.  A pair is
+combined from the pieces that the run boundaries cut its groups into.  The cut is taken when a
+run's length plus COST is at most 19/20 of the static pieces a CU takes one after another.  For
+many random batches (dense layers from one sequence on, sparse layers with selections shorter than
+the budget, host bounds far above the lengths): every group of every pair belongs to exactly one
+piece, a pair's partial slots are exactly 0 .. n-1 and within the workspace's, and no workgroup
+carries much more than an even share.
+"""
+import random
+
+import balanced_cases as BC
+
+COST, KMAX_SPLITS, BAL_MAX_BATCH, TARGET, MIN_GPS, LIST = 8, 64, 64, 256, 8, 1024
+
+
+def cdiv(a, b):
+    return (a + b - 1) // b
+
+
+def host_plan(B, Hkv, N, dense=None):
+    pairs = B * Hkv
+    cap = 32 if pairs < 32 else 16
+    n = min(max(1, cdiv(TARGET, pairs)), max(1, cdiv(N, MIN_GPS)), cap)
+    n_split = cdiv(N, cdiv(N, n))
+    p = dict(n_split=n_split, gps=cdiv(N, n_split), slots=n_split, n_runs=0,
+             rounds=cdiv(n_split * pairs, TARGET))
+    work = pairs * (N + COST)
+    if B > BAL_MAX_BATCH or work >= 1 << 26 or (B == 1 and pairs >= 32):
+        return p
+    slots = max(n_split, cdiv(N, max(MIN_GPS, cdiv(N, cap))) + 1)
+    if dense is not None:
+        if 20 * (cdiv(work, TARGET) + COST) > 19 * (p["gps"] + COST) * p["rounds"]:
+            return p
+        slots = max(n_split, min(slots, dense["slots"]))
+    if slots >= 2:
+        p.update(slots=slots, n_runs=min(n_split * pairs, TARGET))
+    return p
+
+
+def cut(groups, Hkv, N, plan):
+    """Per workgroup: the pieces (b, g, g0, n, slot, n_valid), and whether the cut is balanced.
+    groups: each sequence's 16-row groups (0: an empty sequence)."""
+    groups = [min(max(x, 0), N) for x in groups]
+    B = len(groups)
+    units = [max(1, x) + COST for x in groups]
+    before = [sum(units[:b]) for b in range(B)]
+    W, longest = Hkv * sum(units), max(units) - COST
+    balanced = False
+    if plan["n_runs"] and (B > 1 or 10 * groups[0] < 9 * N):
+        chunk = max(cdiv(W, plan["n_runs"]), MIN_GPS, cdiv(longest, plan["slots"] - 1))
+        balanced = 20 * (chunk + COST) <= 19 * (min(plan["gps"], longest) + COST) * plan["rounds"]
+    out = []
+    if balanced:
+        for w in range(plan["n_runs"]):
+            x, xe, segs = min(w * chunk, W), min((w + 1) * chunk, W), []
+            while x < xe:
+                b = sum(1 for v in before if Hkv * v <= x) - 1
+                g = (x - Hkv * before[b]) // units[b]
+                off = Hkv * before[b] + g * units[b] + COST
+                end = off + units[b] - COST
+                if off >= xe:
+                    break
+                y = max(x, off)
+                first = off // chunk
+                n_valid = (end - 1) // chunk - first + 1
+                segs.append((b, g, y - off, min(xe, end) - y, w - first, n_valid))
+                x = min(xe, end)
+            out.append(segs)
+    else:
+        for b in range(B):
+            for g in range(Hkv):
+                n_valid = max(1, cdiv(groups[b], plan["gps"]))
+                for s in range(n_valid):
+                    g0 = s * plan["gps"]
+                    out.append([(b, g, g0, min(plan["gps"], max(1, groups[b]) - g0), s, n_valid)])
+    return out, balanced
+
+
+def check(groups, Hkv, N, dense=None):
+    plan = host_plan(len(groups), Hkv, N, dense)
+    out, balanced = cut(groups, Hkv, N, plan)
+    seen, slots = {}, {}
+    for segs in out:
+        for b, g, g0, n, slot, n_valid in segs:
+            assert n >= 1 and 0 <= slot < n_valid <= plan["slots"] <= KMAX_SPLITS
+            slots.setdefault((b, g), []).append((slot, n_valid))
+            seen.setdefault((b, g), []).append((g0, g0 + n))
+    for b, x in enumerate(groups):
+        for g in range(Hkv):
+            spans, at = sorted(seen[(b, g)]), 0
+            for lo, hi in spans:
+                assert lo == at
+                at = hi
+            assert at == max(1, min(x, N))
+            got = sorted(slots[(b, g)])
+            assert [s for s, _ in got] == list(range(len(got))) and got[0][1] == len(got)
+    if balanced:
+        loads = [sum(seg[3] + COST for seg in segs) for segs in out if segs]
+        assert max(loads) <= 2 * COST + max(cdiv(sum(loads), plan["n_runs"]) + COST, MIN_GPS,
+                                            cdiv(max(groups), plan["slots"] - 1) + COST) * 2
+    return plan, balanced
+
+
+def test_random_batches_cover_every_group_once():
+    rng, taken = random.Random(7), 0
+    for _ in range(600):
+        B, Hkv, N = rng.randint(1, 70), rng.choice([1, 2, 3, 4, 8]), rng.randint(1, 400)
+        kind = rng.random()
+        if kind < 0.3:
+            groups = [rng.randint(1, N) for _ in range(B)]
+        elif kind < 0.5:
+            groups = [N] * B
+        elif kind < 0.7:   # the host's bound is for a longer generation
+            groups = [rng.randint(1, max(1, N // 4)) for _ in range(B)]
+        else:
+            groups = [rng.choice([0, 1, N, rng.randint(1, N)]) for _ in range(B)]
+        dense = host_plan(B, Hkv, rng.randint(1, 400)) if rng.random() < 0.4 else None
+        taken += check(groups, Hkv, N, dense)[1]
+    assert taken > 150
+
+
+def test_even_batches_keep_the_static_pieces_and_uneven_ones_do_not():
+    for B, Hkv, N in [(16, 8, 2048), (8, 4, 2048), (64, 2, 1152), (64, 2, 65), (1, 8, 512), (32, 8, 2048)]:
+        assert not check([N] * B, Hkv, N)[1]
+    # 160 pairs in two splits are 320 workgroups on 256 CUs; a bound of twice the length
+    assert check([769] * 20, 8, 769)[1]
+    assert check([512], 8, 1024)[1]
+    # a sparse layer of 384 pairs
+    assert check([128] * 48, 8, 128, host_plan(48, 8, 512))[1]
+    assert not check([256] * 16, 8, 256, host_plan(16, 8, 2048))[1]
+
+
+def test_gpu_balanced_batches_take_the_cut():
+    for _, hkv, lens in BC.RAGGED:
+        groups = [cdiv(s, 16) for s in lens]
+        assert check(groups, hkv, max(groups))[1], lens
+    for _, seed in BC.RANDOM:
+        hkv, _, lens = BC.random_case(seed)
+        groups = [cdiv(s, 16) for s in lens]
+        assert check(groups, hkv, max(groups))[1], seed
