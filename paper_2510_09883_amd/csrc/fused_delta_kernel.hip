@@ -354,7 +354,7 @@ __global__ __launch_bounds__(kAttnThreads) void fused_delta_kernel(const FusedAr
     __builtin_amdgcn_s_waitcnt(0);   // the scores written here are complete before selecting
     __syncthreads();
   }
-  select_sequence<kFusedKeysPerThread, U>(a.sel, b);
+  select_sequence<kFusedKeysPerThread, U, kAttnThreads>(a.sel, b);
   if (tid == 0) {
     __hip_atomic_store(&a.counters[(size_t)b * kCounterStride], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(&a.counters[(size_t)b * kCounterStride + 32], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

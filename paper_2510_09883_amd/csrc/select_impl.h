@@ -14,8 +14,6 @@
 
 namespace delta {
 
-constexpr int kSelectThreads = 256;
-constexpr int kSelectWaves = kSelectThreads / 64;
 
 __device__ __forceinline__ uint32_t key_of(float f) {
   return f > 0.f ? __float_as_uint(f) : 0u;   // scores are >= 0; NaN / -0 map to 0
@@ -23,6 +21,7 @@ __device__ __forceinline__ uint32_t key_of(float f) {
 
 // Exclusive prefix sum of one int per thread over the workgroup (one barrier: `s_wave` must not
 // be reused by another scan); *total gets the sum.
+template <int WAVES>
 __device__ __forceinline__ int block_excl_scan(int v, int* s_wave, int* total) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int incl = wave_incl_scan(v);
@@ -30,7 +29,7 @@ __device__ __forceinline__ int block_excl_scan(int v, int* s_wave, int* total) {
   lds_barrier();
   int base = 0, tot = 0;
 #pragma unroll
-  for (int i = 0; i < kSelectWaves; ++i) {
+  for (int i = 0; i < WAVES; ++i) {
     const int c = s_wave[i];
     base += (i < w) ? c : 0;
     tot += c;
@@ -39,7 +38,7 @@ __device__ __forceinline__ int block_excl_scan(int v, int* s_wave, int* total) {
   return base + incl - v;
 }
 
-// Selection for sequence b by one workgroup of kSelectThreads threads.  Thread t owns the
+// Selection for sequence b by one workgroup of THREADS (>= 256) threads.  Thread t owns the
 // candidate keys [t*KPT, t*KPT + KPT) in registers, so index order is thread order then slot
 // order and one block scan places every chosen unit.  KPT (keys per thread) is chosen on the
 // host from the candidate bound.  With a.sel_phys, the physical location of every chosen unit
@@ -47,8 +46,10 @@ __device__ __forceinline__ int block_excl_scan(int v, int* s_wave, int* total) {
 // entries of the thread's keys are loaded together with the keys.  The unit scores are read
 // with device-coherent loads, so they may have been written by other workgroups of the same
 // launch (with device-coherent stores) as well as by an earlier launch.
-template <int KPT, int U>
+template <int KPT, int U, int THREADS>
 __device__ __forceinline__ void select_sequence(const SelectArgs& a, int b) {
+  constexpr int kSelectThreads = THREADS, kSelectWaves = THREADS / 64;
+  static_assert(THREADS >= 256, "a thread for each histogram bin");
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int K = a.budget_units;
@@ -99,8 +100,10 @@ __device__ __forceinline__ void select_sequence(const SelectArgs& a, int b) {
 #pragma unroll
   for (int j = 0; j < KPT; ++j)
     if (!(i0 + j < n_c)) key[j] = 0u;
-  s_hist[0][tid] = 0u;   // kSelectThreads == 256 bins
-  s_hist[1][tid] = 0u;
+  if (tid < 256) {
+    s_hist[0][tid] = 0u;
+    s_hist[1][tid] = 0u;
+  }
   // Bits shared by every candidate key need no histogram: start the digit passes at the
   // highest bit where two keys differ (page scores mostly share sign and high exponent bits,
   // which would otherwise send every key of the first pass to the same bin).
@@ -142,7 +145,7 @@ __device__ __forceinline__ void select_sequence(const SelectArgs& a, int b) {
       if (match) atomicAdd(&hist[(k >> shift) & ((1u << width) - 1u)], 1u);
     }
     lds_barrier();
-    s_hist[(pass + 2) % 3][tid] = 0u;   // for pass + 2 (last read before this pass's barrier)
+    if (tid < 256) s_hist[(pass + 2) % 3][tid] = 0u;   // for pass + 2 (last read before this pass's barrier)
     // Every wave finds the digit itself: lane l owns digits 255-4l .. 252-4l (descending); the
     // lane where the running count from the top reaches `remaining` holds the threshold digit.
     int c[4], sum = 0;
@@ -190,7 +193,7 @@ __device__ __forceinline__ void select_sequence(const SelectArgs& a, int b) {
     n_eq += valid && (key[j] >> low) == T;
   }
   int tot;
-  const int before = block_excl_scan(n_gt | (n_eq << 16), s_wave, &tot);
+  const int before = block_excl_scan<kSelectWaves>(n_gt | (n_eq << 16), s_wave, &tot);
   int eq_rank = before >> 16;
   int pos = (before & 0xffff) + min(eq_rank, remaining);
 #pragma unroll

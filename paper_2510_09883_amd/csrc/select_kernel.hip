@@ -9,7 +9,7 @@
 //   S_u = sum of s_t over the unit's tokens: four tokens per lane and a 4-lane butterfly for
 //   pages, the token itself for token-level units.
 //
-// select_kernel: one 256-thread workgroup per sequence runs the exact radix selection of
+// select_kernel: one workgroup of 256 to 1024 threads per sequence runs the exact radix selection of
 //   select_impl.h (last L units plus the top-(K - L) older units, ties to the lower index).
 #include "internal.h"
 #include "select_impl.h"
@@ -107,9 +107,9 @@ __global__ __launch_bounds__(kScoreThreads) void score_kernel(const ScoreArgs a)
 }
 
 // One workgroup per sequence.
-template <int KPT, int U>
-__global__ __launch_bounds__(kSelectThreads) void select_kernel(const SelectArgs a) {
-  select_sequence<KPT, U>(a, blockIdx.x);
+template <int KPT, int U, int THREADS>
+__global__ __launch_bounds__(THREADS) void select_kernel(const SelectArgs a) {
+  select_sequence<KPT, U, THREADS>(a, blockIdx.x);
 }
 
 __global__ void fill_zero_kernel(uint32_t* p, size_t n_words) {
@@ -151,19 +151,25 @@ hipError_t launch_score(int agg, int unit_tokens, const ScoreArgs& a, int batch,
 
 namespace {
 
+template <int KPT, int U, int THREADS>
+hipError_t launch_select_t(const SelectArgs& a, int batch, hipStream_t stream) {
+  hipLaunchKernelGGL((select_kernel<KPT, U, THREADS>), dim3(batch), dim3(THREADS), 0, stream, a);
+  return hipGetLastError();
+}
+
 template <int U>
 hipError_t launch_select_u(const SelectArgs& a, int batch, hipStream_t stream) {
-  // keys per thread: the smallest power of two covering the candidate bound
   const int bound = a.nu_stride - a.recent_units;
-  const dim3 grid(batch), block(kSelectThreads);
-  if (bound <= 1 * kSelectThreads) hipLaunchKernelGGL((select_kernel<1, U>), grid, block, 0, stream, a);
-  else if (bound <= 2 * kSelectThreads) hipLaunchKernelGGL((select_kernel<2, U>), grid, block, 0, stream, a);
-  else if (bound <= 4 * kSelectThreads) hipLaunchKernelGGL((select_kernel<4, U>), grid, block, 0, stream, a);
-  else if (bound <= 8 * kSelectThreads) hipLaunchKernelGGL((select_kernel<8, U>), grid, block, 0, stream, a);
-  else if (bound <= 16 * kSelectThreads) hipLaunchKernelGGL((select_kernel<16, U>), grid, block, 0, stream, a);
-  else if (bound <= 32 * kSelectThreads) hipLaunchKernelGGL((select_kernel<32, U>), grid, block, 0, stream, a);
-  else return hipErrorInvalidValue;
-  return hipGetLastError();
+  // Keys per thread cost LDS atomics in turn, waves a longer barrier and scan.  Measured on MI355X
+  // with 256, 512 and 1024 threads (us): 872 candidates 3.8, 3.8, 4.2; 1144 candidates of 64
+  // sequences 6.8, 6.0, 5.4; 2040 of 16 6.1, 4.8, 4.9; 4088 8.7, 7.6, 6.0; 7872 tokens 15.5, 10.9, 10.6.
+  if (bound <= 256) return launch_select_t<1, U, 256>(a, batch, stream);
+  if (bound <= 512) return launch_select_t<1, U, 512>(a, batch, stream);
+  if (bound <= 1024) return launch_select_t<2, U, 512>(a, batch, stream);
+  if (bound <= 2048) return launch_select_t<2, U, 1024>(a, batch, stream);
+  if (bound <= 4096) return launch_select_t<4, U, 1024>(a, batch, stream);
+  if (bound <= 8192) return launch_select_t<8, U, 1024>(a, batch, stream);
+  return hipErrorInvalidValue;
 }
 
 }  // namespace
