@@ -22,10 +22,10 @@
 //   * QK^T on the matrix cores: v_mfma_f32_16x16x32_bf16 with A = the 16 K rows (M = rows,
 //     K = head dim) and B = the G query vectors padded to 16 columns; D/32 MFMAs give the
 //     16 x 16 score tile, lane l holding rows 4*(l/16)..+3 of head column l%16.
-//   * online softmax in the log2 domain (exp2, scale folded with log2 e); the group's
-//     probabilities and the per-head rescale factor go through a wave-private LDS slice;
-//   * P.V on the vector ALUs: each lane owns 8 consecutive head-dim columns of 16/RPI rows
-//     (128-bit loads, one V row per LPR consecutive lanes, fully coalesced).
+//   * online softmax in the log2 domain (exp2, scale folded with log2 e), its maximum raised
+//     only when a score exceeds it by 2^8;
+//   * P.V on the matrix cores too, the probabilities split exactly into three bf16 terms that
+//     never leave their lane (attn_tile.h has the layouts and the reasons).
 //   Each wave keeps a ring of R register tiles: while one group is consumed, the K/V loads of
 //   the next R - 1 groups are in flight.  With logits on, the logits of a chunk of groups are
 //   staged in LDS and written by the whole workgroup between chunks.

@@ -21,7 +21,10 @@
 //     4*quad+3 of m, which is the score tile's own layout.  An fp32 probability is the exact sum
 //     of three bf16 terms (its upper 8 significant bits, the next 8, the last 8), and the copies
 //     of a head's column carry one term each: with S = 4 three of the four copies make one MFMA,
-//     with S = 8 two terms make one and the third a second one.  V is bf16 as it is, the products
+//     with S = 8 two terms make one and the third a second one, in which the first copies carry
+//     the first term again (their rows count half in the end): a lower term is often zero, zero
+//     times an infinite V is NaN, and so the rows of the first term, which is zero only where the
+//     probability is, say alone what an infinite V gives (sum_keep_inf).  V is bf16 as it is, the products
 //     are exact and the sums fp32, so no probability is rounded.  Lane (quad, n) loads 8 (d = 128)
 //     or 4 (d = 64) consecutive columns of rows 4*quad .. 4*quad+3, and MFMA c takes column
 //     (D/16)*n + c from lane n: the operand is two byte permutes of the lane's own registers.
@@ -273,13 +276,13 @@ __device__ __forceinline__ void fold_tile(f32x4 acc, Tile<D>& t, float scale_log
   }
   const u32x2 pa = {pack(a1[0], a1[1]), pack(a1[2], a1[3])};
   u32x2 pb = {0u, 0u};
-  if (S == 8) {   // the third term, from the second copies; the first copies' rows get nothing
+  if (S == 8) {   // the third term, from the second copies; the first copies' rows get theirs again
     float a2[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) a2[r] = less_high(a1[r], kHigh);
     pb = u32x2{pack(a2[0], a2[1]), pack(a2[2], a2[3])};
-    pb[0] &= hcol >= S ? 0xffffffffu : 0u;
-    pb[1] &= hcol >= S ? 0xffffffffu : 0u;
+    pb[0] = hcol >= S ? pb[0] : pa[0];
+    pb[1] = hcol >= S ? pb[1] : pa[1];
   }
 #pragma unroll
   for (int c = 0; c < Gm::NC; ++c) {
@@ -371,6 +374,12 @@ struct FloatVec { typedef float type __attribute__((ext_vector_type(W))); };
 template <>
 struct FloatVec<1> { typedef float type; };
 
+// upper * scale + lower of the rows of a first and of lower terms (float2: upper, lower).  Where
+// the upper sum is infinite it is the result: the lower one may be NaN then (see the file header).
+__device__ __forceinline__ float sum_keep_inf(float2 v, float scale = 1.f) {
+  return __builtin_isinf(v.x) ? v.x : fmaf(v.x, scale, v.y);
+}
+
 // The wave's complete sums and outputs: afterwards every lane holds the sum of head hcol % S in
 // l_run, and emit(head, column, w consecutive outputs) has been called for every output of the G
 // heads, each by one lane.  The rows that belong to one head (its terms) stand in different
@@ -391,7 +400,7 @@ __device__ __forceinline__ void reduce_outputs(WaveSoftmax<D, G>& st, int lane, 
         x = lane < 48 ? x : 0.f;
         y = lane < 48 ? y : 0.f;
       }
-      h[c][r] = sum_swap32(x, y);
+      h[c][r] = S == 4 ? sum_keep_inf(swap32(x, y)) : sum_keep_inf(swap32(x, y), 0.5f);
     }
   constexpr int W = S == 4 ? NC / 4 : NC / 2;
   const int col = NC * hcol + (quad >> 1) * (NC / 2) + (S == 4 ? (quad & 1) * (NC / 4) : 0);
@@ -401,7 +410,7 @@ __device__ __forceinline__ void reduce_outputs(WaveSoftmax<D, G>& st, int lane, 
     typename FloatVec<W>::type v;
     float e[W];
 #pragma unroll
-    for (int j = 0; j < W; ++j) e[j] = S == 4 ? sum_swap16(h[j][r], h[j + NC / 4][r]) : h[j][r];
+    for (int j = 0; j < W; ++j) e[j] = S == 4 ? sum_keep_inf(swap16(h[j][r], h[j + NC / 4][r])) : h[j][r];
     __builtin_memcpy(&v, e, sizeof(v));
     if (head < G) emit(head, col, v);
   }

@@ -27,15 +27,15 @@ __device__ __forceinline__ float sum_xor32(float x) {
   return __uint_as_float(p[0]) + __uint_as_float(p[1]);
 }
 
-// Two sums at once: lanes 0-31 get x[l] + x[l + 32], lanes 32-63 y[l - 32] + y[l]; and by rows of
-// 16 lanes, even rows get x[l] + x[l + 16], odd rows y[l - 16] + y[l].
-__device__ __forceinline__ float sum_swap32(float x, float y) {
+// The operands of two reductions at once: lanes 0-31 get (x[l], x[l + 32]), lanes 32-63
+// (y[l - 32], y[l]); and by rows of 16 lanes, even rows (x[l], x[l + 16]), odd rows (y[l - 16], y[l]).
+__device__ __forceinline__ float2 swap32(float x, float y) {
   const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
-  return __uint_as_float(p[0]) + __uint_as_float(p[1]);
+  return make_float2(__uint_as_float(p[0]), __uint_as_float(p[1]));
 }
-__device__ __forceinline__ float sum_swap16(float x, float y) {
+__device__ __forceinline__ float2 swap16(float x, float y) {
   const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
-  return __uint_as_float(p[0]) + __uint_as_float(p[1]);
+  return make_float2(__uint_as_float(p[0]), __uint_as_float(p[1]));
 }
 
 // DPP lane moves inside rows of 16 lanes: x of lane l ^ 1, l ^ 2 (quad permutations) and

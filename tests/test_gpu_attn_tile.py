@@ -61,3 +61,41 @@ def test_tile_step_matches_float64(G, d):
             o, _ = O.full_attention(O.bf16_bits_to_f64(synth.bits(q[b])), K, V, O.default_scale(d))
             err = np.abs(out[b].float().cpu().numpy() - o) - (2.0 ** -8 * np.abs(o) + 2e-3)
             assert err.max() <= 0, f"{kind} G {G} d {d} length {s}: over tolerance by {err.max():.3g}"
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("G", [1, 4, 5, 7, 8])
+def test_infinite_values_stay_infinite(G, d):
+    """A weight times an infinite value is infinite, also where the weight is a power of two, i.e.
+    its lower bf16 terms are zero (one token has weight one); other columns are not touched."""
+    dd = D()
+    g = torch.Generator().manual_seed(7 * G + d)
+    n = [(s + 15) // 16 for s in LENS]
+    pt = torch.zeros((len(LENS), max(n)), dtype=torch.int32)
+    k = (0.1 * torch.randn((sum(n), 1, 16, d), generator=g)).to(torch.bfloat16)
+    v = torch.randn((sum(n), 1, 16, d), generator=g).clamp(-4, 4).to(torch.bfloat16)
+    off = 0
+    for b, s in enumerate(LENS):
+        pt[b, :n[b]] = torch.arange(off, off + n[b])
+        last = off + (s - 1) // 16
+        v[off, 0, 0, 3] = float("inf")
+        v[last, 0, (s - 1) % 16, 20] = -float("inf")
+        v[last, 0, (s - 1) % 16, d - 1] = float("inf")
+        off += n[b]
+    q = torch.randn((len(LENS), G, d), generator=g).to(torch.bfloat16)
+    shape = dd.make_shape(len(LENS), G, 1, d, max(n), max(LENS))
+    dev = [x.cuda() for x in (k, v, pt, torch.tensor(LENS, dtype=torch.int32), q)]
+    out = torch.full_like(dev[4], float("nan"))
+    dd.delta_full_attn(shape, dd.make_kv(*dev[:4]), dev[4], out, dd.alloc_workspace(shape))
+    torch.cuda.synchronize()
+    finite = torch.ones(d, dtype=torch.bool)
+    finite[[3, 20, d - 1]] = False
+    for b, s in enumerate(LENS):
+        o = out[b].float().cpu()
+        assert (o[:, 3] == float("inf")).all() and (o[:, d - 1] == float("inf")).all(), (s, o[:, 3])
+        assert (o[:, 20] == -float("inf")).all(), (s, o[:, 20])
+        K = O.gather_tokens(synth.bits(k), pt[b].numpy(), s)
+        V = np.where(np.isinf(V := O.gather_tokens(synth.bits(v), pt[b].numpy(), s)), 0.0, V)
+        ref, _ = O.full_attention(O.bf16_bits_to_f64(synth.bits(q[b])), K, V, O.default_scale(d))
+        err = (np.abs(o.numpy() - ref) - (2.0 ** -8 * np.abs(ref) + 2e-3))[:, finite.numpy()]
+        assert err.max() <= 0, f"length {s}: over tolerance by {err.max():.3g}"
