@@ -215,10 +215,15 @@ constexpr float kRaise = 8.f;
 template <int D, int G, bool LOGITS>
 __device__ __forceinline__ void fold_tile(f32x4 acc, Tile<D>& t, float scale_log2,
                                           WaveSoftmax<D, G>& st, float* logit_slot, int lane) {
+// Every scaled score is rounded before anything else sees it, the maximum and the stored logit
+// too: with the scaling contracted into the difference's fma, the maximum's own rounding error
+// would be left in the exponent, which for scores of 2^32 and more is a weight of 0 or infinity.
+#pragma clang fp contract(off)
   using Gm = Geo<D>;
   constexpr int S = kCopy<G>;
   const int quad = lane >> 4, hcol = lane & 15;
   const uint32_t kmask = __builtin_amdgcn_readfirstlane(t.kmask);
+  acc *= scale_log2;
   if (kmask != 0xffffu) {   // rows past the end (their K and V may hold NaN)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -229,14 +234,14 @@ __device__ __forceinline__ void fold_tile(f32x4 acc, Tile<D>& t, float scale_log
     }
   }
   if (LOGITS && hcol < G)
-    *reinterpret_cast<f32x4*>(logit_slot + hcol * 16 + 4 * quad) = acc * scale_log2;
+    *reinterpret_cast<f32x4*>(logit_slot + hcol * 16 + 4 * quad) = acc;
 
   float m_use = st.m_run;
   const float mx = fmaxf(fmaxf(acc[0], acc[1]), fmaxf(acc[2], acc[3]));
   // negated, so that a maximum of -inf (nothing folded in yet: inf, or NaN where the tile's
   // scores are -inf too) and NaN scores take the branch
-  if (__any(!(fmaf(mx, scale_log2, -m_use) <= kRaise))) {
-    const float m_new = fmaxf(st.m_run, max_xor32(max_xor16(mx)) * scale_log2);
+  if (__any(!(mx - m_use <= kRaise))) {
+    const float m_new = fmaxf(st.m_run, max_xor32(max_xor16(mx)));
     m_use = (m_new == kNegInfF) ? 0.f : m_new;
     const float alpha = exp2f(st.m_run - m_use);
     st.m_run = m_new;
@@ -256,7 +261,7 @@ __device__ __forceinline__ void fold_tile(f32x4 acc, Tile<D>& t, float scale_log
   }
   float p[4];
 #pragma unroll
-  for (int r = 0; r < 4; ++r) p[r] = __builtin_amdgcn_exp2f(fmaf(acc[r], scale_log2, -m_use));
+  for (int r = 0; r < 4; ++r) p[r] = __builtin_amdgcn_exp2f(acc[r] - m_use);
   st.l_run += (p[0] + p[1]) + (p[2] + p[3]);
 
   // The term of the probabilities that this lane's copy of the head carries: p less the upper

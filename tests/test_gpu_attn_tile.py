@@ -99,3 +99,45 @@ def test_infinite_values_stay_infinite(G, d):
         ref, _ = O.full_attention(O.bf16_bits_to_f64(synth.bits(q[b])), K, V, O.default_scale(d))
         err = (np.abs(o.numpy() - ref) - (2.0 ** -8 * np.abs(ref) + 2e-3))[:, finite.numpy()]
         assert err.max() <= 0, f"length {s}: over tolerance by {err.max():.3g}"
+
+
+def _one_head(K, V, G, lens, q_value=1.0):
+    """Outputs [batch, G, d] of queries of `q_value` over one KV head's keys and values: lists of
+    [s, d] per sequence, one page run each; rows past a sequence's end stay NaN."""
+    dd, d = D(), K[0].shape[1]
+    n = [(s + 15) // 16 for s in lens]
+    pt = torch.zeros((len(lens), max(n)), dtype=torch.int32)
+    k = torch.full((sum(n), 1, 16, d), float("nan"), dtype=torch.bfloat16)
+    v = torch.full_like(k, float("nan"))
+    off = 0
+    for b, s in enumerate(lens):
+        pt[b, :n[b]] = torch.arange(off, off + n[b])
+        for cache, x in ((k, K[b]), (v, V[b])):
+            rows = torch.full((16 * n[b], d), float("nan"), dtype=torch.bfloat16)
+            rows[:s] = x.to(torch.bfloat16)
+            cache[off:off + n[b], 0] = rows.view(-1, 16, d)
+        off += n[b]
+    q = torch.full((len(lens), G, d), q_value, dtype=torch.bfloat16)
+    shape = dd.make_shape(len(lens), G, 1, d, max(n), max(lens))
+    dev = [x.cuda() for x in (k, v, pt, torch.tensor(lens, dtype=torch.int32), q)]
+    out = torch.full_like(dev[4], float("nan"))
+    dd.delta_full_attn(shape, dd.make_kv(*dev[:4]), dev[4], out, dd.alloc_workspace(shape))
+    torch.cuda.synchronize()
+    return out.float().cpu()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("G", [1, 4, 5, 8])
+def test_huge_scores_choose_one_token(G, d):
+    """Scores of 2^13 to 2^97, every token's at least 2^-8 of itself from the next: the highest
+    one has weight 1 and all others 0, so the output is its value, bit for bit."""
+    g = torch.Generator().manual_seed(G + d)
+    for e in (7, 20, 48):
+        mant = torch.stack([1 + torch.arange(128) / 128.0, 2 + torch.arange(128) / 64.0]).flatten()
+        lens = [s for s in LENS if s <= 256]
+        level = [2.0 ** e * mant[torch.randperm(256, generator=g)[:s]] for s in lens]
+        V = [torch.randn((s, d), generator=g).to(torch.bfloat16).float() for s in lens]
+        out = _one_head([x[:, None].expand(-1, d) for x in level], V, G, lens, 2.0 ** e)
+        for b, s in enumerate(lens):
+            want = V[b][level[b].argmax()]
+            assert torch.equal(out[b], want.expand(G, d)), f"2^{e} length {s}: {out[b][0]} for {want}"
