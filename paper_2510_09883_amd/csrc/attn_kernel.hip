@@ -327,10 +327,11 @@ __global__ __launch_bounds__(kAttnThreads, LOGITS ? 1 : 2) void attn_kernel(cons
       }
     }
     auto store_out = [&](const f32x4& v, float lsum, float mx) {
-      const float inv = 1.f / lsum;
+      // (divided, not multiplied by 1 / lsum: that product's extra rounding moves quotients half
+      // way between two bf16 values, as equal weights give)
       uint2 packed;
-      packed.x = (uint32_t)f32_to_bf16_rne(v[0] * inv) | ((uint32_t)f32_to_bf16_rne(v[1] * inv) << 16);
-      packed.y = (uint32_t)f32_to_bf16_rne(v[2] * inv) | ((uint32_t)f32_to_bf16_rne(v[3] * inv) << 16);
+      packed.x = (uint32_t)f32_to_bf16_rne(v[0] / lsum) | ((uint32_t)f32_to_bf16_rne(v[1] / lsum) << 16);
+      packed.y = (uint32_t)f32_to_bf16_rne(v[2] / lsum) | ((uint32_t)f32_to_bf16_rne(v[3] / lsum) << 16);
       *reinterpret_cast<uint2*>(a.out + (size_t)(Hq_row + h) * D + dc) = packed;
       if (LOGITS && dc == 0) a.lse[(size_t)Hq_row + h] = mx + log2f(lsum);
     };

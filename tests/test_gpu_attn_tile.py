@@ -141,3 +141,17 @@ def test_huge_scores_choose_one_token(G, d):
         for b, s in enumerate(lens):
             want = V[b][level[b].argmax()]
             assert torch.equal(out[b], want.expand(G, d)), f"2^{e} length {s}: {out[b][0]} for {want}"
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("G", [1, 8])
+def test_output_is_the_rounded_quotient(G, d):
+    """Equal keys, half of the values one bf16 step above the other half: the sum is exact in fp32
+    and the mean lies half way between the two, so the output is the even one of them."""
+    lens = [2, 14, 30, 94]
+    a = 1 + torch.arange(d) / 128.0
+    V = [torch.where((torch.arange(s) % 2 == 0)[:, None], a, a + 2.0 ** -7) for s in lens]
+    out = _one_head([torch.ones((s, d)) for s in lens], V, G, lens)
+    want = torch.where((torch.arange(d) % 2 == 0), a, a + 2.0 ** -7)     # 128 + j even, or the next
+    for b, s in enumerate(lens):
+        assert torch.equal(out[b], want.expand(G, d)), f"length {s}: {(out[b] != want).sum()} differ"
