@@ -11,20 +11,21 @@
 //     query vectors (N = 16 columns).  Lane (quad, n) of the score tile holds rows 4*quad ..
 //     4*quad+3 of column n.  Column n carries query head n % S, S = 4 (G <= 4) or 8: every head
 //     stands in 16 / S columns, so 16 / S lanes hold the same scores.
-//   * online softmax in the log2 domain (exp2, scale folded with log2 e).  The running maximum is
-//     raised, and the outputs rescaled, only when a score exceeds it by more than kRaise (a
-//     wave-uniform branch, taken a few times per walk); until then the probabilities are
-//     relative to a maximum that is too low by at most 2^kRaise, which fp32 holds with the same
-//     relative precision.  Each lane sums the probabilities of its own rows.
+//   * online softmax in the log2 domain (exp2, scale folded with log2 e).  The cross-lane maximum
+//     and the rescaling of the outputs sit in a wave-uniform branch, taken when a score of the
+//     tile exceeds the running maximum: at most tiles of a walk's beginning, few later on.  (No
+//     probability exceeds 1 then, so sums of large values stay in range.  Letting scores exceed
+//     the maximum by 2^8 before raising it saves 1.5 % of a full layer of one 32K sequence and
+//     of a small step, and nothing from 0.1 GB on.)  Each lane sums the probabilities of its own rows.
 //   * P.V: v_mfma_f32_16x16x16_bf16 with A = P (M = columns n of the score tile, K = the 16 rows)
 //     and B = V (N = 16 head-dim columns).  The A operand's lane (quad, m) holds rows 4*quad ..
 //     4*quad+3 of m, which is the score tile's own layout.  An fp32 probability is the exact sum
 //     of three bf16 terms (its upper 8 significant bits, the next 8, the last 8), and the copies
 //     of a head's column carry one term each: with S = 4 three of the four copies make one MFMA,
-//     with S = 8 two terms make one and the third a second one, in which the first copies carry
-//     the first term again (their rows count half in the end): a lower term is often zero, zero
-//     times an infinite V is NaN, and so the rows of the first term, which is zero only where the
-//     probability is, say alone what an infinite V gives (sum_keep_inf).  V is bf16 as it is, the products
+//     with S = 8 two terms make one and the third a second one, the first copies carrying half of
+//     the first term in each: a lower term is often zero, zero times an infinite V is NaN, and so
+//     the rows of the first term, which is zero only where the probability is, say alone what an
+//     infinite V gives (sum_keep_inf).  V is bf16 as it is, the products
 //     are exact and the sums fp32, so no probability is rounded.  Lane (quad, n) loads 8 (d = 128)
 //     or 4 (d = 64) consecutive columns of rows 4*quad .. 4*quad+3, and MFMA c takes column
 //     (D/16)*n + c from lane n: the operand is two byte permutes of the lane's own registers.
@@ -206,9 +207,6 @@ __device__ __forceinline__ void k_operand(const Tile<D>& t, uint16_t* lk, u32x4 
     ka[ks] = *reinterpret_cast<const u32x4*>(lk + k_slot<D>(lane & 15, 4 * ks + (lane >> 4)));
 }
 
-// A score may exceed the maximum in use by 2^kRaise before the maximum is raised.
-constexpr float kRaise = 8.f;
-
 // Folds one tile's score tile (acc: lane (quad, hcol) holds q_(hcol % S) . k_r for rows
 // r = 4*quad .. 4*quad+3, unscaled) into the wave's softmax state.  With LOGITS, the tile's
 // scaled log2-domain logits go to logit_slot[head][16] (LDS).
@@ -238,9 +236,9 @@ __device__ __forceinline__ void fold_tile(f32x4 acc, Tile<D>& t, float scale_log
 
   float m_use = st.m_run;
   const float mx = fmaxf(fmaxf(acc[0], acc[1]), fmaxf(acc[2], acc[3]));
-  // negated, so that a maximum of -inf (nothing folded in yet: inf, or NaN where the tile's
-  // scores are -inf too) and NaN scores take the branch
-  if (__any(!(mx - m_use <= kRaise))) {
+  // a difference, negated, so that a maximum of -inf (nothing folded in yet: inf, or NaN where the
+  // tile's scores are -inf too) and NaN scores take the branch
+  if (__any(!(mx - m_use <= 0.f))) {
     const float m_new = fmaxf(st.m_run, max_xor32(max_xor16(mx)));
     m_use = (m_new == kNegInfF) ? 0.f : m_new;
     const float alpha = exp2f(st.m_run - m_use);
@@ -269,22 +267,23 @@ __device__ __forceinline__ void fold_tile(f32x4 acc, Tile<D>& t, float scale_log
   // its output rows are dropped in the end.)
   constexpr uint32_t kHigh = 0xffff0000u;
   const uint32_t m1 = hcol >= S ? kHigh : 0u, m2 = hcol >= 2 * S ? kHigh : 0u;
-  auto less_high = [](float x, uint32_t m) { return x - __uint_as_float(__float_as_uint(x) & m); };
+  auto high = [](float x, uint32_t m) { return __uint_as_float(__float_as_uint(x) & m); };
   auto pack = [](float lo, float hi) {   // the upper halves of two floats
     return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
   };
+  const float part = S == 8 && hcol < S ? 0.5f : 1.f;   // (exact, the fma too)
   float a1[4];
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    a1[r] = less_high(p[r], m1);
-    if (S == 4) a1[r] = less_high(a1[r], m2);
+    a1[r] = fmaf(p[r], part, -high(p[r], m1));
+    if (S == 4) a1[r] -= high(a1[r], m2);
   }
   const u32x2 pa = {pack(a1[0], a1[1]), pack(a1[2], a1[3])};
   u32x2 pb = {0u, 0u};
-  if (S == 8) {   // the third term, from the second copies; the first copies' rows get theirs again
+  if (S == 8) {   // the third term, from the second copies; the other half of the first copies' term
     float a2[4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) a2[r] = less_high(a1[r], kHigh);
+    for (int r = 0; r < 4; ++r) a2[r] = a1[r] - high(a1[r], kHigh);
     pb = u32x2{pack(a2[0], a2[1]), pack(a2[2], a2[3])};
     pb[0] = hcol >= S ? pb[0] : pa[0];
     pb[1] = hcol >= S ? pb[1] : pa[1];
@@ -379,10 +378,10 @@ struct FloatVec { typedef float type __attribute__((ext_vector_type(W))); };
 template <>
 struct FloatVec<1> { typedef float type; };
 
-// upper * scale + lower of the rows of a first and of lower terms (float2: upper, lower).  Where
-// the upper sum is infinite it is the result: the lower one may be NaN then (see the file header).
-__device__ __forceinline__ float sum_keep_inf(float2 v, float scale = 1.f) {
-  return __builtin_isinf(v.x) ? v.x : fmaf(v.x, scale, v.y);
+// upper + lower of the rows of a first and of lower terms (float2: upper, lower).  Where the upper
+// sum is infinite it is the result: the lower one may be NaN then (see the file header).
+__device__ __forceinline__ float sum_keep_inf(float2 v) {
+  return __builtin_isinf(v.x) ? v.x : v.x + v.y;
 }
 
 // The wave's complete sums and outputs: afterwards every lane holds the sum of head hcol % S in
@@ -405,7 +404,7 @@ __device__ __forceinline__ void reduce_outputs(WaveSoftmax<D, G>& st, int lane, 
         x = lane < 48 ? x : 0.f;
         y = lane < 48 ? y : 0.f;
       }
-      h[c][r] = S == 4 ? sum_keep_inf(swap32(x, y)) : sum_keep_inf(swap32(x, y), 0.5f);
+      h[c][r] = sum_keep_inf(swap32(x, y));
     }
   constexpr int W = S == 4 ? NC / 4 : NC / 2;
   const int col = NC * hcol + (quad >> 1) * (NC / 2) + (S == 4 ? (quad & 1) * (NC / 4) : 0);

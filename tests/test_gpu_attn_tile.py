@@ -7,6 +7,8 @@ Tolerance: a bf16 output is off by at most 2^-9 of its value, and an fp32 logit 
 (log2 domain) by a few 2^-15, i.e. a weight by some 1e-4 of itself; with |v| <= 4 that leaves
 |o - o_ref| <= 2^-8 |o_ref| + 2e-3.
 """
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -155,3 +157,29 @@ def test_output_is_the_rounded_quotient(G, d):
     want = torch.where((torch.arange(d) % 2 == 0), a, a + 2.0 ** -7)     # 128 + j even, or the next
     for b, s in enumerate(lens):
         assert torch.equal(out[b], want.expand(G, d)), f"length {s}: {(out[b] != want).sum()} differ"
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("G", [1, 4, 5, 8])
+def test_large_finite_values_stay_finite(G, d):
+    """Values up to bf16's largest, 3.3e38, under one token's weight; and 1e38 under weights that
+    rise by 2^6 from one of a wave's pages to the next (2^1.5 a page), so that a maximum raised
+    late, or a term counted twice, would pass fp32's range, which the sums themselves stay below.
+    Tolerance: bf16 rounding, and weights off by 5e-4 of themselves (logits below 2^7)."""
+    g = torch.Generator().manual_seed(3 * G + d)
+    sign = torch.where(torch.rand((d,), generator=g) < 0.5, -1.0, 1.0)
+    for big in (3.3e38, 1e38):
+        K, V = [], []
+        for s in LENS:
+            t = torch.arange(s)
+            top = (t == s - 1) if big > 2e38 else (t % 16 == 0)
+            level = torch.where(top, 1.5 * (t // 16), -80.0)         # log2 of a weight
+            K.append((level * math.log(2) / math.sqrt(d))[:, None].expand(-1, d))
+            V.append(torch.where(top[:, None], big * sign, torch.randn((s, d), generator=g)))
+        out = _one_head(K, V, G, LENS)
+        for b, s in enumerate(LENS):
+            k = K[b].to(torch.bfloat16).double()
+            v = V[b].to(torch.bfloat16).double()
+            ref = torch.softmax(k.sum(1) / math.sqrt(d), 0) @ v
+            err = (out[b].double() - ref).abs() - (2.0 ** -8 * ref.abs() + 5e-4 * big)
+            assert torch.isfinite(out[b]).all() and err.max() <= 0, f"{big:.1e} length {s}: {out[b][0]}"
