@@ -73,7 +73,6 @@ struct SplitPlan {
   int gps = 0;
   int max_groups = 0;
   int slots = 0;         // partial slots per (sequence, kv head)
-  int slots16 = 0;       // the same with at most 16 splits (see Layout::total16)
   int n_runs = 0;        // balanced decomposition: runs (0: not taken)
   int chunk_min = 0;     // balanced decomposition: shortest run
   int static_rounds = 1; // static pieces that a CU takes one after another
@@ -103,20 +102,10 @@ bool plan_split(int batch, int pairs, int max_groups, int slot_cap, const SplitP
   const int want = std::max(1, ceil_div(target, pairs));
   const int most = std::max(1, ceil_div(max_groups, min_groups_per_split()));
   const int cap = max_splits(pairs);
-  auto splits = [&](int limit, int longest) {
-    const int n = std::min(std::min(want, most), limit);
-    return ceil_div(max_groups, std::min(ceil_div(max_groups, n), longest));
-  };
-  p->n_split = splits(cap, max_groups);
+  p->n_split = ceil_div(max_groups, ceil_div(max_groups, std::min(std::min(want, most), cap)));
   p->gps = ceil_div(max_groups, p->n_split);
   p->max_groups = max_groups;
   p->slots = p->n_split;
-  // with at most 16 splits, lists of one piece in LDS at once and one slot more for the pieces of
-  // a ragged batch
-  const int cut16 = std::max(min_groups_per_split(), ceil_div(max_groups, std::min(cap, 16)));
-  p->slots16 = splits(std::min(cap, 16), slot_cap);
-  if (!dense && balance_enabled() && batch >= 2 && batch <= kBalanceMaxBatch && cut16 <= slot_cap)
-    p->slots16 = std::max(p->slots16, ceil_div(max_groups, cut16) + 1);
 
   const int64_t wgs = (int64_t)p->n_split * pairs;
   p->static_rounds = (int)std::min<int64_t>((wgs + target - 1) / target, 1 << 10);
@@ -145,8 +134,6 @@ struct Layout {
   size_t status = 0, counters = 0, part_ml = 0, part_o = 0, logits = 0, lse = 0, uscores = 0, phys = 0;
   size_t fcnt = 0, fflag = 0;
   size_t total = 0;
-  size_t total16 = 0;     // total with at most 16 splits: what the allocation-free step's limit is
-                          // on (its scratch has kNoallocSplitBytes more for the others)
   int fused_chunks = 0;   // chunks per sequence of the fused Delta kernel
   int max_split = 0;
   int logit_pages = 0;
@@ -203,7 +190,6 @@ int make_layout(const delta_shape_t* s, const delta_select_t* sel, Layout* L) {
   if (!plan_split(s->batch, pairs, ceil_div(s->max_seq_len, 16), kMaxRowSlots, nullptr, &L->dense))
     return DELTA_ERR_UNSUPPORTED;
   L->max_split = L->dense.slots;
-  int max_split16 = L->dense.slots16;
   if (sel) {
     const int K = sel->budget_tokens / sel->unit_tokens;
     if (sel->unit_tokens == 16) {
@@ -216,7 +202,6 @@ int make_layout(const delta_shape_t* s, const delta_select_t* sel, Layout* L) {
         return DELTA_ERR_UNSUPPORTED;
     }
     L->max_split = std::max(L->max_split, L->sparse.slots);
-    max_split16 = std::max(max_split16, L->sparse.slots16);
     // the selection holds the older units of one sequence in one workgroup's registers
     if (ceil_div(s->max_seq_len, sel->unit_tokens) - recent_units_of(sel) > kMaxSelectKeys)
       return DELTA_ERR_UNSUPPORTED;
@@ -227,7 +212,6 @@ int make_layout(const delta_shape_t* s, const delta_select_t* sel, Layout* L) {
   if (sel) {
     L->fused_chunks = ceil_div(L->logit_pages, kFusedChunkPages);
     part_splits = std::max(part_splits, L->fused_chunks);
-    max_split16 = std::max(max_split16, L->fused_chunks);
   }
   size_t off = 0;
   L->status = off;    off = align_up(off + sizeof(uint32_t));   // debug builds' status word
@@ -244,11 +228,6 @@ int make_layout(const delta_shape_t* s, const delta_select_t* sel, Layout* L) {
     L->fflag = off;   off = align_up(off + sizeof(int32_t) * (size_t)s->batch * L->fused_chunks);
   }
   L->total = off;
-  auto part_bytes = [&](int splits) {
-    return align_up(sizeof(float) * (size_t)pairs * splits * G * 2) +
-           align_up(sizeof(float) * (size_t)pairs * splits * G * s->head_dim);
-  };
-  L->total16 = L->total - part_bytes(part_splits) + part_bytes(max_split16);
   return DELTA_OK;
 }
 
@@ -616,9 +595,7 @@ int delta_decode_step_noalloc(const delta_shape_t* shape, int32_t n_layers, cons
   Layout L;
   int rc = check_step(shape, n_layers, roles, kv, q, out, sel, sel_idx, sel_cnt, &L);
   if (rc) return rc;
-  // (before any device call)
-  if (L.total16 > kNoallocScratchBytes || L.total > kNoallocScratchBytes + kNoallocSplitBytes)
-    return DELTA_ERR_WORKSPACE;
+  if (L.total > kNoallocScratchBytes) return DELTA_ERR_WORKSPACE;   // before any device call
   void* ws = nullptr;
   if (noalloc_scratch(&ws) != hipSuccess) return DELTA_ERR_HIP;
   char* w = static_cast<char*>(ws);

@@ -152,10 +152,6 @@ hipError_t launch_fill_zero2(void* p0, size_t bytes0, void* p1, size_t bytes1, h
 // GPU (DELTA_NOALLOC_SCRATCH_BYTES of the C ABI), allocated when the step first runs there.
 // *ptr gets the current device's copy.
 constexpr size_t kNoallocScratchBytes = (size_t)160 << 20;
-// Room beside it for the partials of more than 16 splits (fewer than 32 pairs of at most 8 heads of
-// 128: under 24 x 31 x 8 x 130 floats beyond what 16 splits take), so that the limit on a
-// shape's workspace does not depend on the split plan.
-constexpr size_t kNoallocSplitBytes = (size_t)4 << 20;
 hipError_t noalloc_scratch(void** ptr);
 
 }  // namespace delta

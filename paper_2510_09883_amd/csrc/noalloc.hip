@@ -15,7 +15,7 @@
 namespace delta {
 namespace {
 
-static __device__ __align__(256) uint8_t scratch[kNoallocScratchBytes + kNoallocSplitBytes];
+static __device__ __align__(256) uint8_t scratch[kNoallocScratchBytes];
 
 constexpr int kMaxDevices = 64;
 

@@ -2,10 +2,12 @@
 declares, and rejects bad arguments on the host before touching the GPU."""
 import ctypes
 import os
+import random
 import re
 
 import numpy as np
 import pytest
+import torch
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 HEADER = os.path.join(ROOT, "include", "delta_attn.h")
@@ -195,6 +197,41 @@ def test_noalloc_step_rejects_before_any_device_call(D):
     bad_roles = (ctypes.c_int32 * 3)(0, 5, 2)
     assert lib.delta_decode_step_noalloc(P(s), 3, bad_roles, kvs, ptrs, ptrs, P(sel), fake, fake, None) == -1
     assert lib.delta_decode_step_noalloc(P(s), -1, roles, kvs, ptrs, ptrs, P(sel), fake, fake, None) == -1
+
+
+def _noalloc_shapes():
+    """Shapes on both sides of the scratch size: contexts longer than a work list, many and few
+    (sequence, KV head) pairs, with and without a selection, and seeded random ones."""
+    yield 128, 64, 8, 128, 1 << 20, None        # partials only: a few MiB at any length
+    yield 64, 384, 128, 128, 131072, None
+    yield 1, 248, 31, 128, 131072, 2048         # few pairs
+    yield 32, 32, 8, 128, 32768, 2048
+    rng = random.Random(11)
+    for _ in range(400):
+        hkv = rng.choice([1, 2, 4, 8, 16, 31])
+        yield (rng.randint(1, 160), hkv * rng.randint(1, 8), hkv, rng.choice([64, 128]),
+               int(2 ** rng.uniform(6, 17)), rng.choice([None, 256, 2048, 4096]))
+
+
+def test_noalloc_step_refuses_exactly_what_exceeds_its_scratch(D):
+    """DELTA_ERR_WORKSPACE exactly when delta_workspace_bytes() exceeds the documented size.  What
+    is accepted goes on to look the scratch up, which fails without a GPU."""
+    if torch.cuda.is_available():
+        pytest.skip("the accepted calls would run on made-up pointers")
+    P = ctypes.byref
+    fake = ctypes.c_void_p(0x1000)
+    kvs = (D.delta_kv_t * 2)(D.delta_kv_t(1, 2, 3, 4), D.delta_kv_t(1, 2, 3, 4))
+    ptrs = (ctypes.c_void_p * 2)(0x1000, 0x1000)
+    refused = 0
+    for B, hq, hkv, d, s, budget in _noalloc_shapes():
+        shape = D.make_shape(B, hq, hkv, d, -(-s // 16), s)
+        sel = None if budget is None else D.make_select(budget, 128)
+        roles = (ctypes.c_int32 * 2)(0, 0 if sel is None else 1)
+        over = D.delta_workspace_bytes(shape, sel) > D.DELTA_NOALLOC_SCRATCH_BYTES
+        rc = D._lib.delta_decode_step_noalloc(P(shape), 2, roles, kvs, ptrs, ptrs, sel and P(sel), fake, fake, None)
+        assert rc == (D.DELTA_ERR_WORKSPACE if over else D.DELTA_ERR_HIP), (B, hq, hkv, d, s, budget)
+        refused += over
+    assert 40 < refused < 360
 
 
 def test_append_and_hooked_step_reject_before_launch(D):
