@@ -69,6 +69,7 @@ constexpr int kEmptyPage = (int)0x80000000;
 
 template <int D, int G, int MODE, bool LOGITS, bool BAL>
 __global__ __launch_bounds__(kAttnThreads, LOGITS ? 1 : 2) void attn_kernel(const AttnArgs a) {
+  static_assert(!BAL || MODE == ROWS_DENSE, "the balanced decomposition is for dense launches");
   using Gm = Geo<D>;
   constexpr int R = Gm::R;
   constexpr int T = kAttnThreads, NW = T / 64;
@@ -490,11 +491,11 @@ __global__ __launch_bounds__(kAttnThreads, LOGITS ? 1 : 2) void attn_kernel(cons
 
   int bal_chunk = 0;          // > 0: this launch takes the balanced decomposition
   int bal_w = 0, bal_x = 0, bal_xe = 0;   // this workgroup's run [bal_x, bal_xe)
-  // lane l of every wave: sequence l's length, selected units, units of work, and units of work
-  // of sequences 0 .. l - 1
-  int bal_len = 0, bal_n = 0, bal_units = 0, bal_before = 0;
+  // lane l of every wave: sequence l's length, units of work, and units of work of sequences
+  // 0 .. l - 1
+  int bal_len = 0, bal_units = 0, bal_before = 0;
   // (one sequence that nearly fills the host's bound: the static pieces are even)
-  if (BAL && (gridDim.z > 1 || 10 * groups_of(s_bs, sel_ns) < 9 * a.max_groups)) {
+  if (BAL && (gridDim.z > 1 || 10 * groups_of(s_bs, 0) < 9 * a.max_groups)) {
     // Balanced decomposition (the work of a batch spread evenly over the CUs): every (sequence,
     // KV head) pair is kPieceCost units of work followed by its groups, and the pairs, in (b,
     // g) order, are cut into runs of `chunk` units, run w for workgroup w (the launch's linear
@@ -505,15 +506,14 @@ __global__ __launch_bounds__(kAttnThreads, LOGITS ? 1 : 2) void attn_kernel(cons
     const int B = gridDim.z;
     if (lane < B) {
       bal_len = a.seq_lens[lane];
-      if (MODE != ROWS_DENSE) bal_n = min(a.sel_cnt[lane], a.sel_stride);
-      bal_units = max(1, groups_of(bal_len, bal_n)) + kPieceCost;
+      bal_units = max(1, groups_of(bal_len, 0)) + kPieceCost;
     }
     const int incl = wave_incl_scan(bal_units);
     bal_before = incl - bal_units;
     const int total = __builtin_amdgcn_readlane(incl, 63);
     const int longest = (int)wave_max((uint32_t)bal_units) - kPieceCost;
     const int Hkv = a.n_kv_heads;
-    // the host bounds the launch's work units below 2^31
+    // the host bounds the launch's work units below 2^26
     const int W = Hkv * total;
     // (and no pair is cut into more pieces than it has partial slots)
     const int chunk = max(max((W + a.n_runs - 1) / a.n_runs, a.chunk_min),
@@ -557,8 +557,8 @@ __global__ __launch_bounds__(kAttnThreads, LOGITS ? 1 : 2) void attn_kernel(cons
       g0 = x - off;
       ng = min(bal_xe, end) - x;
       s_b = __builtin_amdgcn_readlane(bal_len, b);
-      sel_n = __builtin_amdgcn_readlane(bal_n, b);
-      n_groups = groups_of(s_b, sel_n);
+      sel_n = 0;
+      n_groups = groups_of(s_b, 0);
       bal_x = x + ng;
       if (!(first && b == b_s && g == g_s && g0 == g0_s && min(ng, kSeg) <= cand_s)) {
         if (!first) lds_barrier();   // the previous piece's merge is done with the LDS
@@ -594,33 +594,36 @@ __global__ __launch_bounds__(kAttnThreads, LOGITS ? 1 : 2) void attn_kernel(cons
   }
 }
 
-template <int D, int G, bool BAL>
+template <int D, int G>
 hipError_t launch_dg(int mode, const AttnArgs& a, int batch, hipStream_t stream) {
   const dim3 grid(a.n_split, a.n_kv_heads, batch), block(kAttnThreads);
   switch (mode) {
     case ROWS_DENSE:
-      if (a.logits) hipLaunchKernelGGL((attn_kernel<D, G, ROWS_DENSE, true, BAL>), grid, block, 0, stream, a);
-      else hipLaunchKernelGGL((attn_kernel<D, G, ROWS_DENSE, false, BAL>), grid, block, 0, stream, a);
+      // the balanced decomposition is a separate instantiation, so that launches which cannot
+      // take it run the static kernel's code (0.5-1 us of a launch of 8-12)
+      if (a.logits && a.n_runs > 0) hipLaunchKernelGGL((attn_kernel<D, G, ROWS_DENSE, true, true>), grid, block, 0, stream, a);
+      else if (a.logits) hipLaunchKernelGGL((attn_kernel<D, G, ROWS_DENSE, true, false>), grid, block, 0, stream, a);
+      else if (a.n_runs > 0) hipLaunchKernelGGL((attn_kernel<D, G, ROWS_DENSE, false, true>), grid, block, 0, stream, a);
+      else hipLaunchKernelGGL((attn_kernel<D, G, ROWS_DENSE, false, false>), grid, block, 0, stream, a);
       break;
-    case ROWS_SEL_PAGE: hipLaunchKernelGGL((attn_kernel<D, G, ROWS_SEL_PAGE, false, BAL>), grid, block, 0, stream, a); break;
-    case ROWS_SEL_TOKEN: hipLaunchKernelGGL((attn_kernel<D, G, ROWS_SEL_TOKEN, false, BAL>), grid, block, 0, stream, a); break;
+    case ROWS_SEL_PAGE: hipLaunchKernelGGL((attn_kernel<D, G, ROWS_SEL_PAGE, false, false>), grid, block, 0, stream, a); break;
+    case ROWS_SEL_TOKEN: hipLaunchKernelGGL((attn_kernel<D, G, ROWS_SEL_TOKEN, false, false>), grid, block, 0, stream, a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
-// The balanced decomposition is a separate instantiation, so that launches which cannot take it
-// run the static kernel's code (9 % of an 11 us sparse launch).
 template <int D>
 hipError_t launch_d(int group, int mode, const AttnArgs& a, int batch, hipStream_t stream) {
   switch (group) {
-#define DELTA_ATTN_CASE(G)                                                        \
-  case G:                                                                         \
-    return a.n_runs > 0 ? launch_dg<D, G, true>(mode, a, batch, stream)           \
-                        : launch_dg<D, G, false>(mode, a, batch, stream);
-    DELTA_ATTN_CASE(1) DELTA_ATTN_CASE(2) DELTA_ATTN_CASE(3) DELTA_ATTN_CASE(4)
-    DELTA_ATTN_CASE(5) DELTA_ATTN_CASE(6) DELTA_ATTN_CASE(7) DELTA_ATTN_CASE(8)
-#undef DELTA_ATTN_CASE
+    case 1: return launch_dg<D, 1>(mode, a, batch, stream);
+    case 2: return launch_dg<D, 2>(mode, a, batch, stream);
+    case 3: return launch_dg<D, 3>(mode, a, batch, stream);
+    case 4: return launch_dg<D, 4>(mode, a, batch, stream);
+    case 5: return launch_dg<D, 5>(mode, a, batch, stream);
+    case 6: return launch_dg<D, 6>(mode, a, batch, stream);
+    case 7: return launch_dg<D, 7>(mode, a, batch, stream);
+    case 8: return launch_dg<D, 8>(mode, a, batch, stream);
     default: return hipErrorInvalidValue;
   }
 }

@@ -78,8 +78,8 @@ struct SplitPlan {
   int static_rounds = 1; // static pieces that a CU takes one after another
 };
 
-// Whether launches may spread a batch's work evenly (the balanced decomposition of the attention
-// kernel).  DELTA_ATTN_BALANCE=0 keeps the static one, for comparison.
+// Whether dense launches may spread a batch's work evenly (the balanced decomposition of the
+// attention kernel).  DELTA_ATTN_BALANCE=0 keeps the static one, for comparison.
 bool balance_enabled() {
   static int v = [] {
     const char* e = getenv("DELTA_ATTN_BALANCE");
@@ -89,17 +89,36 @@ bool balance_enabled() {
 }
 
 // Splits per (sequence, kv head) and groups per split for a launch over at most `max_groups`
-// groups of 16 rows, and the balanced decomposition's runs.  Deterministic in the shape, so a
-// FULL and a DELTA call over the same shape use the same plan (and give bitwise-identical
-// outputs).  `dense` is null for full and Delta layers; a sparse layer's groups are its
-// selection's budget, which most sequences have in full, so the host can tell whether the
-// static pieces fill the device evenly, and it shares the dense layers' partial slots.
-bool plan_split(int batch, int pairs, int max_groups, int slot_cap, const SplitPlan* dense,
+// groups of 16 rows, and for full and Delta layers the balanced decomposition's runs (a sparse
+// layer's plan is given the dense one).  Deterministic in the shape, so a FULL and a DELTA call
+// over the same shape use the same plan (and give bitwise-identical outputs).
+//
+// A sparse layer's groups are its selection's budget, which most sequences have in full, so the
+// shape alone says how evenly its static pieces load the CUs, and its output bits depend on
+// nothing else.  Splits are as many as leave one piece per CU: a few CUs without one cost less
+// than a few with two.  Single tokens are gathered row by row, bound by latency, and two pieces
+// per CU hide more of it where a pair has pieces to spare.  Just above one pair per CU, three
+// splits, where one would leave most CUs idle during the second round.
+// Measured on MI355X, us, 8 KV heads, d = 128, G = 4, 128 groups: this rule, the smallest number
+// of pieces that gives every CU one, and the balanced decomposition over the selections.  Pages:
+// 5 sequences 12.0, 15.5, 16.0; 9 16.7, 21.3, 20.3; 20 29.1, 36.4, 34.1; 28 37.3, 41.4, 45.1;
+// 33 54.5, 59.6, 50.5; 40 59.2, 62.0, 59.8.  Tokens: 12 25.5, 29.7; 20 34.0, 40.7, 41.2; 25
+// 43.5, 43.5; one per CU is 26.5, 44.4 and 44.4 there, and 14.2 against two's 14.9 at 5.  With
+// 64 groups three splits and one are 34.0 and 33.0 at 36 sequences, with 128 at 44 68.7 and 63.6.
+bool plan_split(int batch, int pairs, int max_groups, RowMode mode, const SplitPlan* dense,
                 SplitPlan* p) {
   if (max_groups < 1) max_groups = 1;
-  if (ceil_div(max_groups, slot_cap) > kMaxSplits) return false;
+  const int listed = mode == ROWS_SEL_TOKEN ? kMaxRowSlots / 16 : kMaxRowSlots;
+  if (ceil_div(max_groups, listed) > kMaxSplits) return false;
   const int target = target_workgroups();
-  const int want = std::max(1, ceil_div(target, pairs));
+  int want = std::max(1, ceil_div(target, pairs));
+  if (mode != ROWS_DENSE) {
+    const bool two = mode == ROWS_SEL_TOKEN && pairs > 32 && pairs < target;
+    want = std::max(1, (two ? 2 * target : target) / pairs);
+    if (pairs > target && 3 * (int64_t)pairs <= 4 * (int64_t)target && max_groups >= 96) want = 3;
+    // within the workspace that the dense layers take anyway, or one piece per CU
+    want = std::min(want, std::max(dense->slots, ceil_div(target, pairs)));
+  }
   const int most = std::max(1, ceil_div(max_groups, min_groups_per_split()));
   const int cap = max_splits(pairs);
   p->n_split = ceil_div(max_groups, ceil_div(max_groups, std::min(std::min(want, most), cap)));
@@ -113,16 +132,10 @@ bool plan_split(int batch, int pairs, int max_groups, int slot_cap, const SplitP
   // lane and does the cut's arithmetic in 32 bits (20 x the work included), and cuts no pair into
   // more pieces than it has slots.  One sequence with pairs enough has no need of it.
   const int64_t work = (int64_t)pairs * (max_groups + kPieceCost);
-  if (!balance_enabled() || batch > kBalanceMaxBatch || work >= ((int64_t)1 << 26)) return true;
+  if (mode != ROWS_DENSE || !balance_enabled() || batch > kBalanceMaxBatch || work >= ((int64_t)1 << 26)) return true;
   if (batch == 1 && pairs >= 32) return true;
   const int cut = std::max(min_groups_per_split(), ceil_div(max_groups, cap));
-  int slots = std::max(p->n_split, ceil_div(max_groups, cut) + 1);
-  if (dense) {
-    // (the test that the kernel makes with the actual lengths)
-    const int64_t even = (work + target - 1) / target + kPieceCost;
-    if (20 * even > 19 * (int64_t)(p->gps + kPieceCost) * p->static_rounds) return true;
-    slots = std::max(p->n_split, std::min(slots, dense->slots));
-  }
+  const int slots = std::max(p->n_split, ceil_div(max_groups, cut) + 1);
   if (slots < 2) return true;
   p->slots = slots;
   p->n_runs = (int)std::min<int64_t>(wgs, target);
@@ -139,7 +152,7 @@ struct Layout {
   int logit_pages = 0;
   int nu_stride = 0;
   SplitPlan dense, sparse;
-  int sparse_mode = ROWS_SEL_PAGE;
+  RowMode sparse_mode = ROWS_SEL_PAGE;
 };
 
 int check_shape(const delta_shape_t* s) {
@@ -187,20 +200,15 @@ int make_layout(const delta_shape_t* s, const delta_select_t* sel, Layout* L) {
   if (sel && (rc = check_select(sel))) return rc;
   const int pairs = s->batch * s->n_kv_heads;
   const int G = s->n_q_heads / s->n_kv_heads;
-  if (!plan_split(s->batch, pairs, ceil_div(s->max_seq_len, 16), kMaxRowSlots, nullptr, &L->dense))
+  if (!plan_split(s->batch, pairs, ceil_div(s->max_seq_len, 16), ROWS_DENSE, nullptr, &L->dense))
     return DELTA_ERR_UNSUPPORTED;
   L->max_split = L->dense.slots;
   if (sel) {
     const int K = sel->budget_tokens / sel->unit_tokens;
-    if (sel->unit_tokens == 16) {
-      L->sparse_mode = ROWS_SEL_PAGE;
-      if (!plan_split(s->batch, pairs, K, kMaxRowSlots, &L->dense, &L->sparse)) return DELTA_ERR_UNSUPPORTED;
-    } else {
-      L->sparse_mode = ROWS_SEL_TOKEN;
-      if (!plan_split(s->batch, pairs, ceil_div(K, 16), kMaxRowSlots / 16,
-                      &L->dense, &L->sparse))
-        return DELTA_ERR_UNSUPPORTED;
-    }
+    L->sparse_mode = sel->unit_tokens == 16 ? ROWS_SEL_PAGE : ROWS_SEL_TOKEN;
+    if (!plan_split(s->batch, pairs, sel->unit_tokens == 16 ? K : ceil_div(K, 16), L->sparse_mode,
+                    &L->dense, &L->sparse))
+      return DELTA_ERR_UNSUPPORTED;
     L->max_split = std::max(L->max_split, L->sparse.slots);
     // the selection holds the older units of one sequence in one workgroup's registers
     if (ceil_div(s->max_seq_len, sel->unit_tokens) - recent_units_of(sel) > kMaxSelectKeys)

@@ -112,3 +112,31 @@ def test_sparse_layers_of_more_pairs_than_cus(unit, d):
         t = t[t < lens[b]]
         for head in (0, b % hkv, hkv - 1):
             _close(outs[0][b, head:head + 1], _reference(pt, k, v, q, b, t, head, 1)[0], f"sequence {b} head {head}")
+
+
+@pytest.mark.parametrize("unit", [16, 1])
+def test_sparse_bits_depend_on_the_own_sequence_only(unit):
+    """160 pairs: other sequences with fewer selected units, or none, leave a sequence's bits."""
+    dd, B, hkv, hq, d = D(), 20, 8, 32, 128
+    lens = [1100] * B
+    pt, sl, k, v, q = _inputs(lens, hq, hkv, d, 1100, 5)
+    K = 1024 // unit
+    g = torch.Generator().manual_seed(7)
+    idx = torch.stack([torch.randperm(-(-1100 // unit), generator=g)[:K].sort().values for _ in range(B)])
+    idx = idx.to(torch.int32).cuda()
+    shape, sel = dd.make_shape(B, hq, hkv, d, pt.shape[1], 1100), dd.make_select(1024, 16, unit)
+    ws, kv = dd.alloc_workspace(shape, sel), dd.make_kv(k, v, pt, sl)
+    kept = [0, 3, 9, 10, 19]
+    want = None
+    for others in (K, K // 3, 1, 0):
+        cnt = torch.full((B,), others, dtype=torch.int32)
+        cnt[kept] = K
+        out = torch.full_like(q, float("nan"))
+        dd.delta_sparse_attn(shape, kv, q, out, sel, idx, cnt.cuda(), ws)
+        got = out[kept].view(torch.int16)
+        want = got if want is None else want
+        assert torch.equal(got, want), others
+    for b in kept:
+        t = (idx[b, :, None].long() * unit + torch.arange(unit, device="cuda")).flatten()
+        t = t[t < lens[b]]
+        _close(out[b, :4], _reference(pt, k, v, q, b, t, 0, 4)[0], f"sequence {b}")

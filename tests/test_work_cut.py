@@ -1,5 +1,6 @@
 """CPU model of how an attention launch's work is cut (delta_api.cpp plan_split, attn_kernel.hip
-balanced decomposition), checked for the properties the kernel's buffers rely on.
+balanced decomposition), checked for the properties the kernel's buffers rely on.  Sparse layers
+are cut by the shape alone.
 
 Every (sequence, KV head) pair is COST units of work followed by its 16-row groups; the pairs, in
 (sequence, KV head) order, are cut into runs of equal length, run w for workgroup w.  A pair is
@@ -21,21 +22,24 @@ def cdiv(a, b):
     return (a + b - 1) // b
 
 
-def host_plan(B, Hkv, N, dense=None):
+def host_plan(B, Hkv, N, dense=None, tokens=False):
+    """`dense`: the plan of the dense layers, for a sparse layer's plan (of single tokens)."""
     pairs = B * Hkv
     cap = 32 if pairs < 32 else 16
-    n = min(max(1, cdiv(TARGET, pairs)), max(1, cdiv(N, MIN_GPS)), cap)
+    want = cdiv(TARGET, pairs)
+    if dense is not None:
+        want = max(1, (2 if tokens and 32 < pairs < TARGET else 1) * TARGET // pairs)
+        if TARGET < pairs and 3 * pairs <= 4 * TARGET and N >= 96:
+            want = 3
+        want = min(want, max(dense["slots"], cdiv(TARGET, pairs)))
+    n = min(want, max(1, cdiv(N, MIN_GPS)), cap)
     n_split = cdiv(N, cdiv(N, n))
     p = dict(n_split=n_split, gps=cdiv(N, n_split), slots=n_split, n_runs=0,
              rounds=cdiv(n_split * pairs, TARGET))
     work = pairs * (N + COST)
-    if B > BAL_MAX_BATCH or work >= 1 << 26 or (B == 1 and pairs >= 32):
+    if dense is not None or B > BAL_MAX_BATCH or work >= 1 << 26 or (B == 1 and pairs >= 32):
         return p
     slots = max(n_split, cdiv(N, max(MIN_GPS, cdiv(N, cap))) + 1)
-    if dense is not None:
-        if 20 * (cdiv(work, TARGET) + COST) > 19 * (p["gps"] + COST) * p["rounds"]:
-            return p
-        slots = max(n_split, min(slots, dense["slots"]))
     if slots >= 2:
         p.update(slots=slots, n_runs=min(n_split * pairs, TARGET))
     return p
@@ -80,8 +84,8 @@ def cut(groups, Hkv, N, plan):
     return out, balanced
 
 
-def check(groups, Hkv, N, dense=None):
-    plan = host_plan(len(groups), Hkv, N, dense)
+def check(groups, Hkv, N, dense=None, tokens=False):
+    plan = host_plan(len(groups), Hkv, N, dense, tokens)
     out, balanced = cut(groups, Hkv, N, plan)
     seen, slots = {}, {}
     for segs in out:
@@ -119,8 +123,25 @@ def test_random_batches_cover_every_group_once():
         else:
             groups = [rng.choice([0, 1, N, rng.randint(1, N)]) for _ in range(B)]
         dense = host_plan(B, Hkv, rng.randint(1, 400)) if rng.random() < 0.4 else None
-        taken += check(groups, Hkv, N, dense)[1]
+        taken += check(groups, Hkv, N, dense, rng.random() < 0.5)[1]
     assert taken > 150
+
+
+def test_sparse_layers_are_cut_by_the_shape():
+    """Every sequence gets the pieces that it would get alone among full selections, and no CU two
+    pieces of pages while another has none (up to one pair per CU)."""
+    rng = random.Random(3)
+    for _ in range(300):
+        B, Hkv, N = rng.randint(1, 70), rng.choice([1, 2, 4, 8]), rng.randint(1, 300)
+        dense = host_plan(B, Hkv, rng.randint(1, 2000))
+        groups = [rng.choice([N, N, rng.randint(0, N)]) for _ in range(B)]
+        plan, balanced = check(groups, Hkv, N, dense)
+        assert not balanced
+        assert plan["n_split"] * B * Hkv <= TARGET or B * Hkv > TARGET
+        full, _ = cut([N] * B, Hkv, N, plan)
+        mine, _ = cut(groups, Hkv, N, plan)
+        for b in (b for b in range(B) if groups[b] == N):
+            assert [s for s in full if s[0][0] == b] == [s for s in mine if s[0][0] == b]
 
 
 def test_even_batches_keep_the_static_pieces_and_uneven_ones_do_not():
@@ -129,9 +150,6 @@ def test_even_batches_keep_the_static_pieces_and_uneven_ones_do_not():
     # 160 pairs in two splits are 320 workgroups on 256 CUs; a bound of twice the length
     assert check([769] * 20, 8, 769)[1]
     assert check([512], 8, 1024)[1]
-    # a sparse layer of 384 pairs
-    assert check([128] * 48, 8, 128, host_plan(48, 8, 512))[1]
-    assert not check([256] * 16, 8, 256, host_plan(16, 8, 2048))[1]
 
 
 def test_gpu_balanced_batches_take_the_cut():
