@@ -33,3 +33,13 @@ def random_case(seed):
 def batch_limit_lens(B):
     r = random.Random(B)
     return [r.randint(400, 800) for _ in range(B)]
+
+
+# pieces longer than the kernel's list of 1024 pages, listed in parts: (KV heads, lengths, whether
+# the balanced cut is taken), one query head per KV head, and the sequence and head pairs to check
+LONG_PIECES = [(128, [16401, 17000], False, [(0, 0), (1, 77), (1, 127)]),
+               (128, [17000, 33000], True, [(0, 0), (0, 90), (1, 0), (1, 77), (1, 127)])]
+
+# single-token selections (sequences, KV heads, budget, head dim) whose pieces are longer than the
+# list's 64 groups of 16 tokens: 128 groups (walked in blocks of four), 86 and 256
+LONG_TOKEN_PIECES = [(32, 8, 2048, 64, 128), (20, 8, 4096, 128, 86), (48, 8, 4096, 64, 256)]

@@ -9,6 +9,7 @@ sums; logits stay below 2^9); the reference is float64 torch.
 import pytest
 import torch
 
+import balanced_cases as BC
 from gpu_helpers import D
 
 pytestmark = pytest.mark.gpu
@@ -50,8 +51,7 @@ def _close(out, ref, what):
     ([700], 8, 2, 64, 9000, [(0, 0), (0, 1)]),                  # far below the bound
     ([5000], 7, 1, 128, 5000, [(0, 0)]),                        # 32 splits of one pair
     ([4999, 300, 33], 5, 1, 128, 8000, [(0, 0), (1, 0), (2, 0)]),
-    ([16401, 17000], 128, 128, 64, 17000, [(0, 0), (1, 77), (1, 127)]),   # pieces of 1063 groups
-])
+] + [(lens, hkv, hkv, 64, max(lens), check) for hkv, lens, _, check in BC.LONG_PIECES])
 def test_full_and_delta_layers(lens, hq, hkv, d, bound, check):
     dd = D()
     pt, sl, k, v, q = _inputs(lens, hq, hkv, d, bound, len(lens))
@@ -140,3 +140,34 @@ def test_sparse_bits_depend_on_the_own_sequence_only(unit):
         t = (idx[b, :, None].long() * unit + torch.arange(unit, device="cuda")).flatten()
         t = t[t < lens[b]]
         _close(out[b, :4], _reference(pt, k, v, q, b, t, 0, 4)[0], f"sequence {b}")
+
+
+@pytest.mark.parametrize("B,hkv,budget,d,_groups", BC.LONG_TOKEN_PIECES)
+def test_token_pieces_longer_than_the_list(B, hkv, budget, d, _groups):
+    """Pieces of single tokens that are listed in parts, some selections shorter than the budget
+    and not whole groups of 16, with and without stored locations."""
+    dd, s = D(), budget + 100
+    pt, sl, k, v, q = _inputs([s] * B, 2 * hkv, hkv, d, s, budget)
+    g = torch.Generator(device="cuda").manual_seed(B)
+    idx = torch.full((B, budget), -1, dtype=torch.int32, device="cuda")
+    cnt = torch.full((B,), budget, dtype=torch.int32)
+    for b in range(B):
+        if b % 3 == 1:
+            cnt[b] = [budget - 5, 17, 1025, 1][b // 3 % 4]
+        n = int(cnt[b])
+        idx[b, :n] = torch.randperm(s, generator=g, device="cuda")[:n].sort().values.to(torch.int32)
+    u = idx.clamp(min=0).long()
+    phys = torch.where(idx < 0, idx, pt.gather(1, u // 16) * 16 + (u % 16).to(torch.int32)).contiguous()
+    shape, sel = dd.make_shape(B, 2 * hkv, hkv, d, pt.shape[1], s), dd.make_select(budget, 16, 1)
+    ws, kv = dd.alloc_workspace(shape, sel), dd.make_kv(k, v, pt, sl)
+    outs = []
+    for p in (None, phys):
+        out = torch.full_like(q, float("nan"))
+        dd.delta_sparse_attn(shape, kv, q, out, sel, idx, cnt.cuda(), ws, sel_phys=p)
+        outs.append(out)
+    torch.cuda.synchronize()
+    assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))
+    for b in list(range(0, min(B, 14))) + [B - 1]:
+        for head in (0, b % hkv, hkv - 1):
+            ref, _ = _reference(pt, k, v, q, b, idx[b, :int(cnt[b])], head, 2)
+            _close(outs[0][b, 2 * head:2 * head + 2], ref, f"sequence {b} head {head}")

@@ -160,3 +160,15 @@ def test_gpu_balanced_batches_take_the_cut():
         hkv, _, lens = BC.random_case(seed)
         groups = [cdiv(s, 16) for s in lens]
         assert check(groups, hkv, max(groups))[1], seed
+
+
+def test_gpu_long_pieces_are_longer_than_the_list():
+    for hkv, lens, balanced, _ in BC.LONG_PIECES:
+        groups = [cdiv(s, 16) for s in lens]
+        plan, taken = check(groups, hkv, max(groups))
+        out, _ = cut(groups, hkv, max(groups), plan)
+        assert taken == balanced and max(seg[3] for segs in out for seg in segs) > LIST
+    for B, hkv, budget, _, longest in BC.LONG_TOKEN_PIECES:
+        N = budget // 16
+        plan, _ = check([N] * B, hkv, N, host_plan(B, hkv, cdiv(budget + 100, 16)), tokens=True)
+        assert plan["gps"] == longest > LIST // 16
