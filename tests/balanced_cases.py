@@ -1,5 +1,6 @@
-"""The batches the GPU tests of the balanced decomposition run (tests/test_gpu_balanced.py),
-kept in one place so that a CPU test (tests/test_balanced_cut.py) can check that each of them
+"""The batches the GPU tests of the balanced decomposition run (tests/test_gpu_balanced.py,
+tests/test_gpu_work_cut.py),
+kept in one place so that a CPU test (tests/test_work_cut.py) can check that each of them
 really takes the balanced cut.  Plain Python: lengths and shapes only, no arithmetic of the
 method."""
 import random
@@ -34,6 +35,9 @@ def batch_limit_lens(B):
     r = random.Random(B)
     return [r.randint(400, 800) for _ in range(B)]
 
+
+# sequences so short that a run spans up to three pairs (8 KV heads)
+SHORT_PIECES = [1 + 37 * i % 290 for i in range(48)]
 
 # pieces longer than the kernel's list of 1024 pages, listed in parts: (KV heads, lengths, whether
 # the balanced cut is taken), one query head per KV head, and the sequence and head pairs to check

@@ -1,16 +1,16 @@
 """GPU parity of the balanced decomposition of dense (full and Delta) launches: a ragged
 batch's 16-row groups, in (sequence, KV head, page) order, are cut into equal runs, one per
-workgroup, and a run may hold the end of one (sequence, KV head) pair and the start of the next.
-The cut is taken only where it shortens the longest run by a tenth against the static pieces;
-equal lengths keep the static split (the CPU model of the cut, tests/test_balanced_cut.py,
+CU, and a run may hold the end of one (sequence, KV head) pair and the start of the next.
+The cut is taken only where it shortens a CU's longest share by a twentieth against the static
+pieces; equal lengths keep the static split (the CPU model of the cut, tests/test_work_cut.py,
 says which cases take it).
 
-Llama-8B attention shape, six sequences of 1.8K-4K tokens: the launch has 288 workgroups
-(6 splits of 43 groups over 48 pairs), the batch 8920 groups, so every run is 31 groups and the
-pairs (113 to 256 groups) are each combined from 5 to 10 pieces cut at places that do not
-depend on the pair.  Qwen-7B shape with twelve sequences of 65-1455 tokens: runs of 8 groups
-(against static pieces of 16), so some runs hold a whole short pair (written directly, no
-combine) and parts of its neighbours, three pairs in one run.  Eight seeded random shapes
+Llama-8B attention shape, six sequences of 1.8K-4K tokens: statically 288 workgroups (6 splits of
+43 groups over 48 pairs) on 256 CUs; the batch's 8920 groups, with 8 units of work more per pair,
+make runs of 37 units, and the pairs (113 to 256 groups) are each combined from 4 to 8 pieces cut
+at places that do not depend on the pair.  Qwen-7B shape with twelve sequences of 65-1455 tokens:
+runs of 8 units (against static pieces of 16), so that a short pair is one piece (written directly,
+no combine) and a long one up to 13.  Eight seeded random shapes
 (group sizes 1-8, head dims 64 and 128, 2-8 KV heads, 6-24 sequences of lengths in [L/4, L],
 shuffled page tables on odd seeds) cover the other kernel instantiations.  Outputs and
 selections are checked against the oracle, and the Delta layer's output against the full
@@ -72,7 +72,7 @@ def test_balanced_runs_match_oracle(cid, lens):
 def _random_case(seed, G):
     """A seeded random shape with group size G (tests/balanced_cases.py; shuffled page tables
     on odd seeds).  The seeds are ones whose batch takes the balanced cut, which
-    tests/test_balanced_cut.py checks on the CPU model of the cut."""
+    tests/test_work_cut.py checks on the CPU model of the cut."""
     hkv, d, lens = BC.random_case(seed)
     w = configs.Workload(90 + seed, f"random{seed}", 3, G * hkv, hkv, d, len(lens), max(lens), 256,
                          hh_frac=0.02, shuffled_pages=bool(seed % 2),

@@ -51,6 +51,7 @@ def _close(out, ref, what):
     ([700], 8, 2, 64, 9000, [(0, 0), (0, 1)]),                  # far below the bound
     ([5000], 7, 1, 128, 5000, [(0, 0)]),                        # 32 splits of one pair
     ([4999, 300, 33], 5, 1, 128, 8000, [(0, 0), (1, 0), (2, 0)]),
+    (BC.SHORT_PIECES, 16, 8, 64, max(BC.SHORT_PIECES), [(0, 0), (7, 7), (8, 1), (30, 4), (47, 7)]),
 ] + [(lens, hkv, hkv, 64, max(lens), check) for hkv, lens, _, check in BC.LONG_PIECES])
 def test_full_and_delta_layers(lens, hq, hkv, d, bound, check):
     dd = D()
