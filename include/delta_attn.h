@@ -35,11 +35,13 @@
  *             delta_full_attn's on the same inputs when it runs the split path (with the fused
  *             DELTA kernel, see DELTA_PATH_*, the two agree up to floating-point summation
  *             order).
- *             FULL and DELTA calls over 2 to 64 sequences split the batch's work evenly over
- *             the GPU from the actual sequence lengths, so a sequence's output bits (never
- *             its accuracy) can depend on the other sequences' lengths in the same call;
+ *             FULL and DELTA calls over up to 64 sequences split their work evenly over the
+ *             GPU from the actual sequence lengths, so a sequence's output bits (never its
+ *             accuracy) can depend on the other sequences' lengths in the same call;
  *             DELTA_ATTN_BALANCE=0 in the environment (read once per process) keeps the
- *             per-sequence split, whose bits depend on the sequence and the shape only.
+ *             per-sequence split, whose bits depend on the sequence and the shape only, as
+ *             those of SPARSE calls always do.
+ *             A softmax weight below 2^-126 of its head's largest may count as zero.
  *   Workspace. `ws` is caller-owned device memory of at least delta_workspace_bytes() bytes.
  *             It must be zero-filled once after allocation; every call leaves it ready for the
  *             next call with the same shape and selection parameters.  Calls with another

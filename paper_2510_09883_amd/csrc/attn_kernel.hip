@@ -15,15 +15,16 @@
 // one for each CU, each run possibly spanning pairs: for ragged batches, lengths far below the
 // host's bound, and pair counts that would leave CUs with one static piece more than others
 // (20 sequences of 12289 tokens with 8 KV heads are 320 static workgroups on 256 CUs: 183 us
-// against 165).  Waves take a piece's groups in turn and keep their own online-softmax state;
-// all G query heads of the KV group share every K/V byte read.
+// against 159).  Full and Delta launches only: sparse ones are cut by the shape.  Waves take a
+// piece's groups in turn and keep their own online-softmax state; all G query heads of the KV
+// group share every K/V byte read.
 //
 // Per group and wave:
 //   * QK^T on the matrix cores: v_mfma_f32_16x16x32_bf16 with A = the 16 K rows (M = rows,
-//     K = head dim) and B = the G query vectors padded to 16 columns; D/32 MFMAs give the
-//     16 x 16 score tile, lane l holding rows 4*(l/16)..+3 of head column l%16.
-//   * online softmax in the log2 domain (exp2, scale folded with log2 e), its maximum raised
-//     only when a score exceeds it by 2^8;
+//     K = head dim) and B = the G query vectors, each in two or four of the 16 columns; D/32
+//     MFMAs give the 16 x 16 score tile, lane l holding rows 4*(l/16)..+3 of column l%16.
+//   * online softmax in the log2 domain (exp2, scale folded with log2 e), the wave's maximum
+//     formed only for tiles that raise it;
 //   * P.V on the matrix cores too, the probabilities split exactly into three bf16 terms that
 //     never leave their lane (attn_tile.h has the layouts and the reasons).
 //   Each wave keeps a ring of R register tiles: while one group is consumed, the K/V loads of
@@ -169,7 +170,7 @@ __global__ __launch_bounds__(kAttnThreads, LOGITS ? 1 : 2) void attn_kernel(cons
     // Loads tile `li` of the listed groups (the first is group l0 of the pair).  `row` is its
     // page list entry (page modes), read from LDS one tile ahead.  A prefetch past the wave's
     // last group (real == false) is still issued, so that the loop's memory waits stay uniform,
-    // but reads one cache line per load instruction instead of a whole tile.
+    // but reads nothing (a page tile) or one cache line per load instruction (gathered rows).
     const int s_last_page = (s_b - 1) >> 4;
     const uint32_t tail_mask = 0xffffu >> (15 - ((s_b - 1) & 15));   // rows of the last page
     auto load_tile = [&](Tile<D>& t, int row, int li, int l0, bool real) {

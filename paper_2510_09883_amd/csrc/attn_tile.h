@@ -13,10 +13,11 @@
 //     stands in 16 / S columns, so 16 / S lanes hold the same scores.
 //   * online softmax in the log2 domain (exp2, scale folded with log2 e).  The cross-lane maximum
 //     and the rescaling of the outputs sit in a wave-uniform branch, taken when a score of the
-//     tile exceeds the running maximum: at most tiles of a walk's beginning, few later on.  (No
+//     tile exceeds the running maximum: for most tiles at a walk's beginning, few later on.  (No
 //     probability exceeds 1 then, so sums of large values stay in range.  Letting scores exceed
-//     the maximum by 2^8 before raising it saves 1.5 % of a full layer of one 32K sequence and
-//     of a small step, and nothing from 0.1 GB on.)  Each lane sums the probabilities of its own rows.
+//     the maximum by 2^8 before raising it saves 1.5 % of a full layer of one 32K sequence and of
+//     a round of one 8K sequence, and nothing from 0.1 GB on.)  Each lane sums the probabilities
+//     of its own rows.  A weight below 2^-126 of the largest counts as zero (v_exp_f32).
 //   * P.V: v_mfma_f32_16x16x16_bf16 with A = P (M = columns n of the score tile, K = the 16 rows)
 //     and B = V (N = 16 head-dim columns).  The A operand's lane (quad, m) holds rows 4*quad ..
 //     4*quad+3 of m, which is the score tile's own layout.  An fp32 probability is the exact sum
@@ -35,9 +36,14 @@
 // sum per tile) and uncoalesced K loads the chain took 1.1 us per 8 KB tile, i.e. 29 GB/s per CU
 // with one wave per SIMD however many loads were in flight, while a CU alone reads 57 GB/s: grids
 // below 256 workgroups and the few tiles per wave of small launches were bound by it.  Measured
-// on MI355X, before and after (us per layer): one 32K sequence, 28/4 heads, 64 workgroups 43.5 and
-// 26.6; 64 sequences of 600-1500 tokens, 12/2 heads 26.5 and 20.0; 20 sequences of 12289 tokens,
-// 40/8 heads 219 and 183; 32 ragged sequences of 16K-32K, 32/8 heads (3.2 GB) 501 and 485.
+// on MI355X, before and after the tile alone, the work cut the same (us per layer): one 32K
+// sequence, 28/4 heads, 64 workgroups 43.5 and 26.6; 64 sequences of 600-1500 tokens, 12/2 heads
+// 26.5 and 20.0; 20 sequences of 12289 tokens, 40/8 heads 219 and 183; 32 ragged sequences of
+// 16K-32K, 32/8 heads (3.2 GB, at the memory rate either way) 494 and 493.
+//
+// The split of an fp32 operand into bf16 terms is that of Henry, Tang and Heinecke, "Leveraging the
+// bfloat16 Artificial Intelligence Datatype For Higher-Precision Computations" (2019), the online
+// softmax that of Milakov and Gimelshein, "Online normalizer calculation for softmax" (2018).
 #pragma once
 
 #include "internal.h"

@@ -56,9 +56,9 @@ int min_groups_per_split() {
 // and each split adds an arrival on the same counter, so beyond ~16 splits the combine costs
 // more than the shorter loop saves where the pairs fill the device anyway; with fewer than 32
 // pairs (256 workgroups at 8 splits each and more) the splits are what fills it, up to 32.  Measured
-// on MI355X with 16 and 32 splits: one 32K sequence with 4 KV heads 26.9 and 22.0 us, one 128K
-// sequence with 8 KV heads 103.7 and 89.2; 64 splits gave 22.8 and 91.4.  DELTA_ATTN_MAX_SPLITS
-// overrides it for tuning.
+// on MI355X with 16, 32 and 64 splits, us: one 32K sequence with 4 KV heads 26.9, 22.0 and 22.8,
+// one 128K sequence with 8 KV heads 103.7, 89.2 and 91.4 (with a merge by one thread group; the
+// first takes 20.1 now).  DELTA_ATTN_MAX_SPLITS overrides it for tuning.
 int max_splits(int pairs) {
   static int v = [] {
     const char* e = getenv("DELTA_ATTN_MAX_SPLITS");

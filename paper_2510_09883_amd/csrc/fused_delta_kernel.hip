@@ -88,7 +88,7 @@ __global__ __launch_bounds__(kAttnThreads) void fused_delta_kernel(const FusedAr
     st.init();
     const size_t head_off = (size_t)g * 16 * D;
     float* lg = s_logit + (size_t)g * kC * G * 16;
-    // ring of R tiles as in the split kernel; prefetches past the chunk are one-line dummies
+    // ring of R tiles as in the split kernel; prefetches past the chunk read nothing
     auto fetch = [&](Tile<D>& t, int k) {
       const int kk = min(k, np - 1);
       const size_t page = (size_t)__builtin_amdgcn_readfirstlane(s_pages[kk]) * a.page_stride + head_off;

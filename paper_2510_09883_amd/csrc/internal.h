@@ -23,14 +23,14 @@ enum RowMode {
 };
 
 // Hard limits of the attention kernel's on-chip staging.
-constexpr int kAttnThreads = 256;        // fused Delta kernel: 4 waves of 64
+constexpr int kAttnThreads = 256;        // attention and fused Delta kernel: 4 waves of 64
 constexpr int kMaxSplits = 64;           // split partials combined by the last workgroup
 constexpr int kMaxRowSlots = 1024;       // LDS slots staging a piece's page / row list
 constexpr int kPieceCost = 8;            // fixed cost of a piece in groups (restaging, ring refill,
                                          // merge: about 2.5 us, a group 0.3 us of a CU's time)
-constexpr int kMaxGroup = 8;             // query heads per KV head (padded to 16 MFMA columns)
+constexpr int kMaxGroup = 8;             // query heads per KV head (copied to 16 MFMA columns)
 constexpr int kMaxSelectKeys = 8192;     // candidate units one selection workgroup holds in registers
-constexpr int kBalanceMaxBatch = 64;     // sequences of a balanced dense launch (one per lane)
+constexpr int kBalanceMaxBatch = 64;     // sequences of a balanced launch (one per lane)
 // Ints between consecutive arrival counters (256 bytes): every counter that many workgroups
 // update and poll sits in a memory block of its own instead of sharing one with its neighbours'.
 constexpr int kCounterStride = 64;

@@ -38,16 +38,12 @@ __device__ __forceinline__ float2 swap16(float x, float y) {
   return make_float2(__uint_as_float(p[0]), __uint_as_float(p[1]));
 }
 
-// DPP lane moves inside rows of 16 lanes: x of lane l ^ 1, l ^ 2 (quad permutations) and
-// l ^ 8 (rotation of the row by 8).
+// DPP lane moves inside rows of 16 lanes: x of lane l ^ 1 and l ^ 2 (quad permutations).
 __device__ __forceinline__ float lane_xor1(float x) {
   return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0xB1, 0xf, 0xf, false));
 }
 __device__ __forceinline__ float lane_xor2(float x) {
   return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x4E, 0xf, 0xf, false));
-}
-__device__ __forceinline__ float lane_xor8(float x) {
-  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x128, 0xf, 0xf, false));
 }
 
 // Inclusive prefix sum over the 64 lanes: row shifts by 1, 2, 4, 8 (lanes shifted in from
