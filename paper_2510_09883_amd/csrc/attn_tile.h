@@ -15,9 +15,10 @@
 //     and the rescaling of the outputs sit in a wave-uniform branch, taken when a score of the
 //     tile exceeds the running maximum: for most tiles at a walk's beginning, few later on.  (No
 //     probability exceeds 1 then, so sums of large values stay in range.  Letting scores exceed
-//     the maximum by 2^8 before raising it saves 1.5 % of a full layer of one 32K sequence and of
-//     a round of one 8K sequence, and nothing from 0.1 GB on.)  Each lane sums the probabilities
-//     of its own rows.  A weight below 2^-126 of the largest counts as zero (v_exp_f32).
+//     the maximum by 2^8 before raising it saves 1.5 % of a full layer of one 32K sequence and 3 %
+//     of a sparse layer of 2-4 tiles per wave (11.1 us), and nothing from 0.1 GB on.)  Each lane
+//     sums the probabilities of its own rows.  A weight below 2^-126 of the largest counts as zero
+//     (v_exp_f32).
 //   * P.V: v_mfma_f32_16x16x16_bf16 with A = P (M = columns n of the score tile, K = the 16 rows)
 //     and B = V (N = 16 head-dim columns).  The A operand's lane (quad, m) holds rows 4*quad ..
 //     4*quad+3 of m, which is the score tile's own layout.  An fp32 probability is the exact sum
