@@ -47,3 +47,10 @@ LONG_PIECES = [(128, [16401, 17000], False, [(0, 0), (1, 77), (1, 127)]),
 # single-token selections (sequences, KV heads, budget, head dim) whose pieces are longer than the
 # list's 64 groups of 16 tokens: 128 groups (walked in blocks of four), 86 and 256
 LONG_TOKEN_PIECES = [(32, 8, 2048, 64, 128), (20, 8, 4096, 128, 86), (48, 8, 4096, 64, 256)]
+
+# sparse launches at the edges of their split rule (sequences, KV heads, budget, unit, splits): three
+# splits just above one pair per CU (96 groups, and one at 95), one pair per CU and one piece less,
+# most splits, two pieces per CU for single tokens from 33 to 255 pairs
+SPARSE_SPLITS = [(33, 8, 1536, 16, 3), (33, 8, 1520, 16, 1), (32, 8, 512, 16, 1), (43, 3, 512, 16, 1),
+                 (1, 1, 4096, 16, 32), (11, 3, 1024, 1, 8), (4, 8, 1024, 1, 8), (51, 5, 512, 1, 2),
+                 (64, 4, 512, 1, 1)]

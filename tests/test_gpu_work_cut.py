@@ -143,23 +143,25 @@ def test_sparse_bits_depend_on_the_own_sequence_only(unit):
         _close(out[b, :4], _reference(pt, k, v, q, b, t, 0, 4)[0], f"sequence {b}")
 
 
-@pytest.mark.parametrize("B,hkv,budget,d,_groups", BC.LONG_TOKEN_PIECES)
-def test_token_pieces_longer_than_the_list(B, hkv, budget, d, _groups):
-    """Pieces of single tokens that are listed in parts, some selections shorter than the budget
-    and not whole groups of 16, with and without stored locations."""
-    dd, s = D(), budget + 100
+@pytest.mark.parametrize("B,hkv,budget,d,unit", [(*c[:4], 1) for c in BC.LONG_TOKEN_PIECES]
+                         + [(*c[:3], 64, c[3]) for c in BC.SPARSE_SPLITS])
+def test_sparse_pieces(B, hkv, budget, d, unit):
+    """Pieces of single tokens that are listed in parts, and the edges of the sparse split rule; some
+    selections shorter than the budget and not whole groups, with and without stored locations."""
+    dd, s, K = D(), budget + 100, budget // unit
     pt, sl, k, v, q = _inputs([s] * B, 2 * hkv, hkv, d, s, budget)
     g = torch.Generator(device="cuda").manual_seed(B)
-    idx = torch.full((B, budget), -1, dtype=torch.int32, device="cuda")
-    cnt = torch.full((B,), budget, dtype=torch.int32)
+    idx = torch.full((B, K), -1, dtype=torch.int32, device="cuda")
+    cnt = torch.full((B,), K, dtype=torch.int32)
     for b in range(B):
         if b % 3 == 1:
-            cnt[b] = [budget - 5, 17, 1025, 1][b // 3 % 4]
+            cnt[b] = [K - 5, 17, K // 2 + 1, 1][b // 3 % 4]
         n = int(cnt[b])
-        idx[b, :n] = torch.randperm(s, generator=g, device="cuda")[:n].sort().values.to(torch.int32)
+        idx[b, :n] = torch.randperm(-(-s // unit), generator=g, device="cuda")[:n].sort().values.to(torch.int32)
     u = idx.clamp(min=0).long()
-    phys = torch.where(idx < 0, idx, pt.gather(1, u // 16) * 16 + (u % 16).to(torch.int32)).contiguous()
-    shape, sel = dd.make_shape(B, 2 * hkv, hkv, d, pt.shape[1], s), dd.make_select(budget, 16, 1)
+    phys = pt.gather(1, u) if unit == 16 else pt.gather(1, u // 16) * 16 + (u % 16).to(torch.int32)
+    phys = torch.where(idx < 0, idx, phys).contiguous()
+    shape, sel = dd.make_shape(B, 2 * hkv, hkv, d, pt.shape[1], s), dd.make_select(budget, 16, unit)
     ws, kv = dd.alloc_workspace(shape, sel), dd.make_kv(k, v, pt, sl)
     outs = []
     for p in (None, phys):
@@ -168,7 +170,9 @@ def test_token_pieces_longer_than_the_list(B, hkv, budget, d, _groups):
         outs.append(out)
     torch.cuda.synchronize()
     assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))
-    for b in list(range(0, min(B, 14))) + [B - 1]:
+    for b in sorted({*range(min(B, 14)), B - 1}):
+        t = (idx[b, :int(cnt[b]), None].long() * unit + torch.arange(unit, device="cuda")).flatten()
+        t = t[t < s]
         for head in (0, b % hkv, hkv - 1):
-            ref, _ = _reference(pt, k, v, q, b, idx[b, :int(cnt[b])], head, 2)
+            ref, _ = _reference(pt, k, v, q, b, t, head, 2)
             _close(outs[0][b, 2 * head:2 * head + 2], ref, f"sequence {b} head {head}")

@@ -215,3 +215,10 @@ def test_gpu_long_pieces_are_longer_than_the_list():
         N = budget // 16
         plan, _ = check([N] * B, hkv, N, host_plan(B, hkv, cdiv(budget + 100, 16)), tokens=True)
         assert plan["gps"] == longest > LIST // 16
+
+
+def test_gpu_sparse_splits_are_the_rule_s():
+    for B, hkv, budget, unit, n_split in BC.SPARSE_SPLITS:
+        N, dense = budget // 16, host_plan(B, hkv, cdiv(budget + 100, 16))
+        plan, _ = check([N] * B, hkv, N, dense, tokens=unit == 1)
+        assert plan["n_split"] == n_split, (B, hkv, budget, unit, plan)
